@@ -12,44 +12,53 @@
 //   q -> q_out [T, Hq, D];  k -> K cache [blk][g][slot][d];
 //   v -> V cache [blk][g][slot][d]
 //
-// Design (one workgroup = 8 wavefronts = one 256-feature x 256-token tile):
+// Design (persistent workgroups of 8 wavefronts, one per CU, walking tiles of
+// 256 features x 256 tokens):
 //  * The product is formed as C^T = W x^T with v_mfma_f32_16x16x32_bf16:
 //    A = 16 rows of W, B = 16 token rows of x, 32 hidden per instruction. In
 //    the 16x16 accumulator a lane holds one token and 4 consecutive features,
 //    so everything the epilogue needs per element (position, block, slot) is
 //    per lane. This shape sustains a higher rate than 32x32x16 on random data
 //    (the card's power limit lowers the clock less for it).
-//  * Wave (wf, wt) owns features {j0 .. j0 + 31} and {j0 + D/2 .. + 31} of one
-//    head (four 16-row blocks) and 128 tokens (eight 16-token blocks). The
-//    blocks j0 + 16 p and j0 + D/2 + 16 p are exactly rotary pairs
-//    (j, j + D/2), which therefore sit in the same lane and register of two
-//    accumulators: the rotation needs no data exchange.
-//  * Hidden is walked in steps of 64 (two MFMA k-steps). Two LDS stages of
-//    64 KB (256 W rows then 256 x rows, 128 bytes each) are filled by
-//    LDS-direct loads (global_load_lds, no registers) one step ahead of their
-//    use; one barrier per step. Each load instruction brings 8 whole 128-byte
-//    rows (copies of whole lines out of L2 run at several times the rate of
-//    half-line copies). The 16-byte chunk c of LDS row r holds global chunk
-//    c ^ ((r >> 1) & 7), so the 16 rows read by one operand load hit distinct
-//    banks. An odd count of 32 hidden ends with a half step whose upper
-//    chunks are not used.
-//  * Within a step a wave loads the first k-step's operands, then issues its
-//    products in groups of one token block, each group followed by operand
-//    loads of the second k-step and one of the next step's copies; then the
-//    second k-step's products. The copies are inline asm, which the compiler
-//    does not track: tracked LDS-direct loads make it wait for every LDS read
-//    before the first product.
+//  * A wave owns features {j0 .. j0 + 31} and {j0 + D/2 .. + 31} of one head
+//    (four 16-row blocks) and 128 tokens (eight 16-token blocks). The two
+//    halves are rotary pairs (j, j + D/2) in the same lane and register of two
+//    accumulators: the rotation needs no data exchange. The rows of a pair of
+//    blocks are staged interleaved (staged_feature), so that a lane's elements
+//    of both are 8 consecutive features: one 16-byte store.
+//  * Hidden is walked in steps of 64 (two MFMA k-steps). LDS is a ring of five
+//    32 KB slots that hold the W rows and the x rows of a step in turn (256
+//    rows of one 128-byte line each), filled by load-to-LDS copies (no
+//    registers) about two steps ahead; the copies run on across tiles, so the
+//    next tile's first steps arrive during a tile's epilogue. Each copy brings
+//    8 whole lines (half-line copies run at a fraction of the rate). The
+//    16-byte chunk c of LDS row r holds global chunk c ^ ((r >> 1) & 7), so the
+//    16 rows read by one operand load hit distinct banks.
+//  * The two waves of a SIMD (w and w + 4) alternate: while one issues the 32
+//    products of a k-step, the other reads its next operands from LDS and
+//    issues copies; a workgroup barrier ends each interval, and the second
+//    group runs one interval behind the first. The matrix pipe then always has
+//    one wave feeding it, instead of waiting at each step's barrier for every
+//    wave's first operands. Both k-steps' W operands are read in the first
+//    interval (16 and 8 operand loads), which frees the W slot a step early.
 //  * Tiles are numbered XCD-major (workgroup b runs on XCD b % 8), and within
 //    an XCD feature tiles vary fastest in groups of 8, so the workgroups that
 //    run together on one L2 share their W and x rows.
 //  * fp32 accumulation; bias, rotation (fp32 cos/sin from a table the host
 //    computes in fp64) and one bf16 rounding in the epilogue.
+// Bound: the matrix pipe under the card's power limit (the clock falls to about
+// 1.7 GHz on random data, 2.39 on zeros). T = 16,128, hidden 4,096, 6,144
+// features (812 GFLOP): 579 us, 1.40 PFLOP/s; with one barrier per step for all
+// waves, a 2-stage ring and one workgroup per tile it took 678 us (same card).
+// A tile takes 138 k cycles for its 64 steps (131 k of them products of the two
+// waves of a SIMD) and 9 k for its epilogue.
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
 #include <string>
+#include <type_traits>
 
 #include "cw_internal.h"
 
@@ -57,30 +66,38 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) void lds_void_t;
+typedef const __attribute__((address_space(4))) int32_t cint32_t;
 
 constexpr int kThreads = 512;                  // 8 wavefronts
-constexpr int kTileF = 256;                    // output features per workgroup
-constexpr int kTileT = 256;                    // tokens per workgroup
+constexpr int kTileF = 256;                    // output features per tile
+constexpr int kTileT = 256;                    // tokens per tile
 constexpr int kStep = 64;                      // hidden elements per pipeline step
 constexpr int kRow = kStep * 2;                // bytes of one staged row (one 128-byte line)
-constexpr int kPartW = kTileF * kRow;          // 32 KB: the W rows of a stage
-constexpr int kStage = kPartW + kTileT * kRow; // + 32 KB of x rows
-constexpr int kStages = 2;
-constexpr int kAhead = kStages - 1;            // steps in flight (the loop's waits assume one)
-constexpr int kCopiesW = kPartW / 1024 / 8;    // 1 KB LDS-direct copies per wave and step: W rows
-constexpr int kCopiesX = kTileT * kRow / 1024 / 8;   // and x rows
-constexpr int kCopies = kCopiesW + kCopiesX;
+constexpr int kSlot = 256 * kRow;              // 32 KB: the W rows or the x rows of a step
+constexpr int kSlots = 5;
+constexpr int kOwn = kSlot / 8;                // a wave's part of a slot
 constexpr int kGroupF = 8;                     // feature tiles per XCD group
 constexpr int kBs = cw::kBlockSize;
-static_assert(kCopiesW == 4 && kCopiesX == 4, "8 rows per copy, 32 W and 32 x rows per wave");
-static_assert(kStages * kStage <= 160 * 1024, "LDS of one CU");
-static_assert(kAhead == 1, "each step waits for all of its copies");
+static_assert(kTileF == 256 && kTileT == 256, "32 W and 32 x rows per wave, four 8-row copies each");
+static_assert(kSlots * kSlot <= 160 * 1024, "LDS of one CU");
+
+struct QkvArgs {
+  const uint8_t* x;
+  const uint8_t* w;
+  const uint16_t* bias;
+  const float* rope;
+  uint16_t* q_out;
+  uint16_t* k_cache;
+  uint16_t* v_cache;
+  const int32_t* bt;
+  const int32_t* cu;
+  const int32_t* plen;
+  int T, hidden, n_feat, bt_stride, batch, hq, hkv, num_blocks;
+  int n_ftiles, n_ttiles, per_xcd;
+};
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
@@ -89,12 +106,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
 
-// One load-to-LDS copy: lane l's 16 bytes at src land at dst + 16 l (dst
-// wave-uniform, through M0). The compiler does not count it: the kernel's own
-// waits complete it.
-__device__ __forceinline__ void copy16_to_lds(const void* src, lds_void_t* dst) {
-  const uint32_t m = __builtin_amdgcn_readfirstlane(uint32_t(reinterpret_cast<uintptr_t>(dst)));
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(src), "s"(m) : "memory");
+// One load-to-LDS copy: lane l's 16 bytes at base + off land at dst + 16 l
+// (base and dst wave-uniform, dst through M0). The compiler does not count it:
+// the kernel's own waits complete it.
+__device__ __forceinline__ void copy16_to_lds(const uint8_t* base, uint32_t off, uint32_t dst) {
+  const uint64_t b = reinterpret_cast<uintptr_t>(base);
+  const uint64_t bu = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b >> 32)))) << 32) |
+                      uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b))));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(off), "s"(bu), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
 }
 
 // s_waitcnt immediates (gfx9 encoding): vmcnt(n) with lgkmcnt(0), expcnt untouched.
@@ -105,62 +125,234 @@ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | (7 << 4) | ((n >> 4) <
 // positions per row parity.
 __device__ __forceinline__ int row_swz(int r) { return (r >> 1) & 7; }
 
+// Feature staged at LDS row s: within each 32 rows, block b = s / 16 of the
+// MFMA's 16 rows holds features 8 g + 4 b + e at row 4 g + e, so that a lane's
+// accumulator elements of blocks 0 and 1 are 8 consecutive features.
+__device__ __forceinline__ int staged_feature(int s) {
+  return (s & ~31) | ((s & 12) << 1) | ((s & 16) >> 2) | (s & 3);
+}
+
+// Workgroup barrier that no memory access or instruction group moves across.
+__device__ __forceinline__ void interval_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Bias, rotation, rounding and stores of one wave's results: features j0 ..
+// j0 + 16 FH - 1 of head hf and their partners at + D/2, for the NTB 16-token
+// blocks from token tw on (tokens before t_own are another tile's). Element e
+// of acc[fa][tb] is feature j0 + 4 FH g + 4 (fa % FH) + e (+ D/2 for fa >= FH)
+// of token tw + 16 tb + l16, with g = lane / 16, l16 = lane % 16. `own`: 1 KB x
+// 2 FH of LDS no other wave uses.
+//
+// Lane l first works out position and destination of tokens tw + 64 i + l: the
+// request of the first token by bisection over cu, then the requests that
+// start inside the wave's tokens (scalar loads). The rotation's cos/sin rows
+// are loaded whole, one token block ahead (128 FH contiguous bytes per token: a
+// load that takes each lane's own 16 bytes touches four times as many lines
+// per instruction, and the loads' line rate bounds the epilogue: 11 k cycles
+// against 9 k), and reach their lanes through `own`.
+template <int D, int FH, int NTB>
+__device__ __forceinline__ void store_results(const QkvArgs& a, f32x4 (&acc)[2 * FH][NTB], int hf, int j0, int tw,
+                                              int t_own, uint8_t* own, int lane) {
+  if (hf >= a.hq + 2 * a.hkv) return;
+  cint32_t* const cu = reinterpret_cast<cint32_t*>(reinterpret_cast<uintptr_t>(a.cu));
+  cint32_t* const plen = reinterpret_cast<cint32_t*>(reinterpret_cast<uintptr_t>(a.plen));
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int kind = hf < a.hq ? 0 : (hf < a.hq + a.hkv ? 1 : 2);   // q, k, v
+  const int g = kind == 1 ? hf - a.hq : hf - a.hq - a.hkv;
+  constexpr int NM = (NTB + 3) / 4;   // tokens per lane
+  int lo = 0, hi = a.batch - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (cu[mid] <= tw) lo = mid;
+    else hi = mid - 1;
+  }
+  int req[NM], shift[NM];   // request, and its position minus token
+#pragma unroll
+  for (int i = 0; i < NM; ++i) {
+    req[i] = lo;
+    shift[i] = plen[lo] - cu[lo];
+  }
+  for (int r = lo + 1; r < a.batch; ++r) {
+    const int c = cu[r];
+    if (c >= tw + 16 * NTB || c >= a.T) break;
+    const int sh = plen[r] - c;
+#pragma unroll
+    for (int i = 0; i < NM; ++i)
+      if (tw + 64 * i + lane >= c) {
+        req[i] = r;
+        shift[i] = sh;
+      }
+  }
+  int pos[NM];        // position, -1 where nothing is written
+  uint64_t dst[NM];   // address of the token's row of head hf
+#pragma unroll
+  for (int i = 0; i < NM; ++i) {
+    const int t = tw + 64 * i + lane;
+    const int p = min(t, a.T - 1) + shift[i];
+    bool ok = t < a.T && t >= t_own;
+    if (kind == 0) {
+      dst[i] = reinterpret_cast<uintptr_t>(a.q_out) + (uint64_t(uint32_t(t)) * uint32_t(a.hq) + uint32_t(hf)) * (2 * D);
+    } else {
+      const int blk = ok ? a.bt[int64_t(req[i]) * a.bt_stride + p / kBs] : -1;
+      ok = blk >= 0 && blk < a.num_blocks;
+      dst[i] = reinterpret_cast<uintptr_t>(kind == 1 ? a.k_cache : a.v_cache) +
+               ((uint64_t(uint32_t(blk)) * uint32_t(a.hkv) + uint32_t(g)) * kBs + (p & (kBs - 1))) * (2 * D);
+    }
+    pos[i] = ok ? p : -1;
+  }
+  const int j = j0 + 4 * FH * g4;   // the lane's first feature
+  if (a.bias) {
+#pragma unroll
+    for (int fa = 0; fa < 2 * FH; ++fa) {
+      const uint16_t* bp = a.bias + int64_t(hf) * D + (fa / FH) * (D / 2) + j + 4 * (fa % FH);
+      const uint64_t v = *reinterpret_cast<const uint64_t*>(bp);
+      const f32x4 b{bf16_lo(uint32_t(v)), bf16_hi(uint32_t(v)), bf16_lo(uint32_t(v >> 32)), bf16_hi(uint32_t(v >> 32))};
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) acc[fa][tb] += b;
+    }
+  }
+  auto finish = [&](auto rotate) __attribute__((always_inline)) {
+    constexpr bool kRotate = decltype(rotate)::value;
+    constexpr int CH = 8 * FH;   // 16-byte chunks of a token's cos/sin pairs
+    f32x4 nx[2 * FH], cs[2 * FH];
+    auto load_cs = [&](int tb) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 2 * FH; ++i) {
+        const int p = max(__shfl(pos[tb >> 2], (tb & 3) * 16 + (64 / CH) * i + lane / CH), 0);
+        nx[i] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const uint8_t*>(a.rope) +
+                                                uint64_t(uint32_t(p)) * (4 * D) + (j0 * 8 + (lane % CH) * 16));
+      }
+    };
+    if constexpr (kRotate) load_cs(0);
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb) {
+      if constexpr (kRotate) {
+        // chunk c of token r at position c ^ (r % CH) of its row
+#pragma unroll
+        for (int i = 0; i < 2 * FH; ++i) {
+          const int r = (64 / CH) * i + lane / CH;
+          *reinterpret_cast<f32x4*>(own + r * (16 * CH) + (((lane % CH) ^ (r % CH)) << 4)) = nx[i];
+        }
+        asm volatile("" ::: "memory");   // other lanes' writes: not to be forwarded past
+        if (tb + 1 < NTB) load_cs(tb + 1);
+#pragma unroll
+        for (int i = 0; i < 2 * FH; ++i)
+          cs[i] = *reinterpret_cast<const f32x4*>(own + l16 * (16 * CH) + (((2 * FH * g4 + i) ^ (l16 % CH)) << 4));
+        asm volatile("" ::: "memory");
+      }
+      const int ps = __shfl(pos[tb >> 2], (tb & 3) * 16 + l16);
+      const uint32_t dlo = __shfl(uint32_t(dst[tb >> 2]), (tb & 3) * 16 + l16);
+      const uint32_t dhi = __shfl(uint32_t(dst[tb >> 2] >> 32), (tb & 3) * 16 + l16);
+      uint32_t o0[2 * FH], o1[2 * FH];
+#pragma unroll
+      for (int e = 0; e < 2 * FH; ++e) {
+        float a0 = acc[e >> 1][tb][(e & 1) * 2], a1 = acc[e >> 1][tb][(e & 1) * 2 + 1];
+        float b0 = acc[FH + (e >> 1)][tb][(e & 1) * 2], b1 = acc[FH + (e >> 1)][tb][(e & 1) * 2 + 1];
+        if constexpr (kRotate) {
+          const f32x4 r = cs[e];   // cos, sin of two rotary indices
+          const float ra = a0 * r[0] - b0 * r[1], rb = b0 * r[0] + a0 * r[1];
+          const float sa = a1 * r[2] - b1 * r[3], sb = b1 * r[2] + a1 * r[3];
+          a0 = ra;
+          b0 = rb;
+          a1 = sa;
+          b1 = sb;
+        }
+        o0[e] = pack_bf16x2(a0, a1);
+        o1[e] = pack_bf16x2(b0, b1);
+      }
+      if (ps >= 0) {
+        uint32_t* dp = reinterpret_cast<uint32_t*>(((uint64_t(dhi) << 32) | dlo) + 2 * j);
+        typedef uint32_t vec_t __attribute__((ext_vector_type(2 * FH)));
+        vec_t v0, v1;
+#pragma unroll
+        for (int e = 0; e < 2 * FH; ++e) {
+          v0[e] = o0[e];
+          v1[e] = o1[e];
+        }
+        *reinterpret_cast<vec_t*>(dp) = v0;
+        *reinterpret_cast<vec_t*>(dp + D / 4) = v1;
+      }
+    }
+  };
+  if (kind != 2) finish(std::true_type{});
+  else finish(std::false_type{});
+}
+
+// First feature and token of tile L: feature tiles vary fastest in groups of
+// kGroupF, the token tiles within a group.
+__device__ __forceinline__ void tile_origin(const QkvArgs& a, int L, int tile_f, int tile_t, int& f0, int& t0) {
+  const int grp = L / (kGroupF * a.n_ttiles);
+  const int gf = min(kGroupF, a.n_ftiles - grp * kGroupF);
+  const int rem = L - grp * kGroupF * a.n_ttiles;
+  t0 = (rem / gf) * tile_t;
+  f0 = (grp * kGroupF + rem % gf) * tile_f;
+}
+
 template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void qkv_rope_append_kernel(const uint8_t* __restrict__ x, const uint8_t* __restrict__ w,
-                            const uint16_t* __restrict__ bias, const float* __restrict__ rope,
-                            int T, int hidden, int n_feat, uint16_t* __restrict__ q_out,
-                            uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
-                            const int32_t* __restrict__ bt, int bt_stride, const int32_t* __restrict__ cu,
-                            const int32_t* __restrict__ plen, int batch, int hq, int hkv, int num_blocks,
-                            int n_ftiles, int n_ttiles, int per_xcd) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[kStages * kStage];
+void qkv_rope_append_kernel(const QkvArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kSlots * kSlot];
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
 
-  // ---- tile of this workgroup
-  const int b = blockIdx.x;
-  const int L = (b & 7) * per_xcd + (b >> 3);
-  if (L >= n_ftiles * n_ttiles) return;
-  const int grp = L / (kGroupF * n_ttiles);
-  const int gf = min(kGroupF, n_ftiles - grp * kGroupF);
-  const int rem = L - grp * kGroupF * n_ttiles;
-  const int tt = rem / gf;
-  const int ft = grp * kGroupF + rem % gf;
-  const int f0 = ft * kTileF;
-  const int t0 = tt * kTileT;
+  // ---- this workgroup's tiles: every 32nd tile of its XCD's range
+  const int xcd = blockIdx.x & 7, wg_per_xcd = gridDim.x >> 3;
+  const int tile_end = min((xcd + 1) * a.per_xcd, a.n_ftiles * a.n_ttiles);
+  int tile = xcd * a.per_xcd + (blockIdx.x >> 3);
+  if (tile >= tile_end) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int l32 = lane & 31;
-  const int half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- staging role: W rows 32 wave .. + 31 and x rows 32 wave .. + 31 of
-  // each step; copy i brings 8 rows, lane l chunk l % 8 of row l / 8 (LDS
-  // position l % 8 holds global chunk (l % 8) ^ row_swz(row)).
-  const int64_t hb = int64_t(hidden) * 2;   // bytes per row of W and x
-  const uint8_t* src[kCopies];
-  int chunk[kCopies];
+  // ---- copy cursor: the tile and step whose rows are copied next. A tile that
+  // would reach past the last row of W or x is moved back to end there (its
+  // first rows are then another tile's, and not stored), so the lane offsets
+  // are the same for every tile.
+  const int64_t hb = int64_t(a.hidden) * 2;   // bytes per row of W and x
+  const int nk = (a.hidden + kStep - 1) / kStep;
+  // the last step holds 32 hidden: it is moved back to the row's last 64 and
+  // uses their upper half (a row of 32 has both halves copied from it)
+  const bool half_last = (a.hidden % kStep) != 0;
+  const int f_max = max(a.n_feat - kTileF, 0), t_max = max(a.T - kTileT, 0);
+  int c_tile = tile, c_step = 0;
+  const uint8_t *c_w, *c_x;
+  uint32_t offw[4], offx[4];
 #pragma unroll
-  for (int i = 0; i < kCopies; ++i) {
-    const int row = i < kCopiesW ? 32 * wave + 8 * i + (lane >> 3) : 32 * wave + 8 * (i - kCopiesW) + (lane >> 3);
-    chunk[i] = (lane & 7) ^ row_swz(row);
-    src[i] = i < kCopiesW ? w + int64_t(min(f0 + row, n_feat - 1)) * hb : x + int64_t(min(t0 + row, T - 1)) * hb;
+  for (int i = 0; i < 4; ++i) {
+    const int row = 32 * wave + 8 * i + (lane >> 3);
+    int c = ((lane & 7) ^ row_swz(row)) * 16;
+    if (a.hidden < kStep) c &= ~64;
+    offw[i] = uint32_t(min(staged_feature(row), a.n_feat - 1)) * uint32_t(hb) + c;
+    offx[i] = uint32_t(min(row, a.T - 1)) * uint32_t(hb) + c;
   }
-  const int nk = (hidden + kStep - 1) / kStep;
-  const bool half_last = (hidden % kStep) != 0;   // the last step holds 32 hidden
-  // copy i of a step into stage st
-  auto issue_one = [&](int step, int st, int i) __attribute__((always_inline)) {
-    uint8_t* dst = lds + st * kStage;
-    // (past the row's end in a half step the lane copies the chunk 4 below,
-    // which nothing reads)
-    const bool cut = half_last && step == nk - 1;
-    const int c = (cut && chunk[i] >= 4) ? chunk[i] - 4 : chunk[i];
-    const int off = i < kCopiesW ? (32 * wave + 8 * i) * kRow : kPartW + (32 * wave + 8 * (i - kCopiesW)) * kRow;
-    copy16_to_lds(src[i] + int64_t(step) * kRow + c * 16, (lds_void_t*)(dst + off));
+  auto cursor_tile = [&]() __attribute__((always_inline)) {
+    int f0, t0;
+    tile_origin(a, c_tile, kTileF, kTileT, f0, t0);
+    c_w = a.w + int64_t(min(f0, f_max)) * hb;
+    c_x = a.x + int64_t(min(t0, t_max)) * hb;
   };
-  auto issue = [&](int step, int st) __attribute__((always_inline)) {
+  cursor_tile();
+  // the W (x) rows of the cursor's step into ring slot `slot`
+  auto issue4 = [&](const uint8_t* base, const uint32_t (&off)[4], int slot) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + slot * kSlot + wave * kOwn;
 #pragma unroll
-    for (int i = 0; i < kCopies; ++i) issue_one(step, st, i);
+    for (int i = 0; i < 4; ++i) copy16_to_lds(base, off[i], dst + i * 1024);
+  };
+  auto cursor_next = [&]() __attribute__((always_inline)) {
+    if (++c_step < nk) {
+      const int d = (half_last && c_step == nk - 1) ? kRow / 2 : kRow;
+      c_w += d;
+      c_x += d;
+    } else if (c_tile + wg_per_xcd < tile_end) {
+      c_tile += wg_per_xcd;
+      c_step = 0;
+      cursor_tile();
+    }   // past the last tile: its last step again, which nothing reads
   };
 
   // ---- operand rows of this wave
@@ -172,144 +364,103 @@ void qkv_rope_append_kernel(const uint8_t* __restrict__ x, const uint8_t* __rest
   const int brow = wt * 128;
   const int l16 = lane & 15;
   const int g4 = lane >> 4;
-  // 16-row block starting at a multiple of 16 rows, k-step ks of the stage:
+  // 16-row block starting at a multiple of 16 rows, k-step ks of the slot:
   // lane reads row l16, chunk 4 ks + g4 (swizzled)
   const int so0 = l16 * kRow + ((g4 ^ row_swz(l16)) << 4);
   const int so1 = l16 * kRow + (((4 + g4) ^ row_swz(l16)) << 4);
-  // feature blocks: fa = 0, 1 -> j0 + 16 fa; fa = 2, 3 -> j0 + D/2 + 16 (fa - 2)
-  int arow[4];
-#pragma unroll
-  for (int fa = 0; fa < 4; ++fa) arow[fa] = arow0 + (fa >> 1) * (D / 2) + (fa & 1) * 16;
+  // feature blocks: fa = 0, 1 -> rows j0 + 16 fa; fa = 2, 3 -> j0 + D/2 + 16 (fa - 2)
+  auto arow = [&](int fa) { return arow0 + (fa >> 1) * (D / 2) + (fa & 1) * 16; };
+  auto ld = [&](int addr) __attribute__((always_inline)) -> bf16x8 {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + addr));
+  };
 
   f32x4 acc[4][8];
+  auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int fa = 0; fa < 4; ++fa)
+    for (int fa = 0; fa < 4; ++fa)
 #pragma unroll
-    for (int tb = 0; tb < 8; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int tb = 0; tb < 8; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
 
+  // ---- the first two steps' copies; the second is left in flight
 #pragma unroll
-  for (int s = 0; s < kAhead; ++s)
-    if (s < nk) issue(s, s);
-
-  for (int k = 0; k < nk; ++k) {
-    // this step's copies have landed, in every wave; then the stage of step
-    // k - 1 is free for step k + 1
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    // the next step's copies go out with the first k-step's products (in the
-    // last step they copy that step's rows again into the free stage: the
-    // loop's end waits for them)
-    const int nxt = min(k + kAhead, nk - 1);
-
-    // The first k-step's operands, then its products in groups of one token
-    // block (4 MFMAs), each followed by loads of the second k-step's operands
-    // into the registers the group has consumed; then the second k-step's
-    // products. Scheduling barriers keep this order. A half step loads the
-    // second k-step's operands too and skips its products.
-    const uint8_t* st = lds + (k % kStages) * kStage;
-    auto ld = [&](int row, int so) __attribute__((always_inline)) -> bf16x8 {
-      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + row * kRow + so));
-    };
-    bf16x8 a0[4], a1[4], bx[8];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int fa = 0; fa < 4; ++fa) a0[fa] = ld(arow[fa], so0);
-#pragma unroll
-    for (int tb = 0; tb < 8; ++tb) bx[tb] = ld(kTileF + brow + 16 * tb, so0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int tb = 0; tb < 8; ++tb) {
-#pragma unroll
-      for (int fa = 0; fa < 4; ++fa)
-        acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[fa], bx[tb], acc[fa][tb], 0, 0, 0);
-      bx[tb] = ld(kTileF + brow + 16 * tb, so1);
-      if (tb < 4) a1[tb] = ld(arow[tb], so1);
-      issue_one(nxt, (k + kAhead) % kStages, tb);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (!(half_last && k == nk - 1)) {
-#pragma unroll
-      for (int tb = 0; tb < 8; ++tb) {
-#pragma unroll
-        for (int fa = 0; fa < 4; ++fa)
-          acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[fa], bx[tb], acc[fa][tb], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+  for (int i = 0; i < 2; ++i) {
+    issue4(c_w, offw, 2 * i);
+    issue4(c_x, offx, 2 * i + 1);
+    cursor_next();
   }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(8));
+  interval_barrier();
+  if (wt == 1) interval_barrier();   // the second group runs one interval behind
 
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-
-  // ---- epilogue: bias, rotation, bf16 rounding, stores
-  const int hf = (f0 + head_l * D) / D;
-  if (hf >= hq + 2 * hkv) return;
-  const int kind = hf < hq ? 0 : (hf < hq + hkv ? 1 : 2);
-  const int g = kind == 1 ? hf - hq : hf - hq - hkv;
-  // element e of acc[fa][tb]: feature j0 + 16 (fa & 1) + 4 g4 + e (+ D/2 for fa >= 2), token brow + 16 tb + l16
-  float bb[4][4];
+  // Slots: step s (counted over all tiles) keeps its W rows in slot 2 s % 5 and
+  // its x rows in slot (2 s + 1) % 5. Numbering the intervals so that group 0
+  // reads in intervals 4 s and 4 s + 2 of step s and group 1 in 4 s + 1 and
+  // 4 s + 3:
+  //  - the W copies of step s + 2 go out from interval 4 s on, into the slot of
+  //    x of step s - 1, last read (by group 1) in interval 4 s - 1;
+  //  - the x copies of step s + 2 go out from interval 4 s + 2 on, into the slot
+  //    of W of step s, last read in interval 4 s + 1;
+  //  - a wave's copies of step s + 1 have landed at the end of its second
+  //    reading interval of step s (8 younger copies stay in flight), at most
+  //    4 s + 3; the barrier after it lets interval 4 s + 4 read them.
+  // A reading interval ends with lgkmcnt(0), so its reads are complete at its
+  // barrier.
+  int slot = 0, free_slot = 0;
+  auto inc = [](int v) { return v + 1 == kSlots ? 0 : v + 1; };
+  for (; tile < tile_end; tile += wg_per_xcd) {
+    for (int k = 0; k < nk; ++k) {
+      const int sx = inc(slot), s2 = inc(sx), s4 = inc(inc(s2));
+      const int wst = slot * kSlot, xst = sx * kSlot;
+      bf16x8 af[2][4], bx[8];
 #pragma unroll
-  for (int fa = 0; fa < 4; ++fa) {
-    if (bias) {
-      const u32x2 v = *reinterpret_cast<const u32x2*>(bias + int64_t(hf) * D + j0 + (fa >> 1) * (D / 2) + (fa & 1) * 16 + 4 * g4);
-      bb[fa][0] = bf16_lo(v[0]); bb[fa][1] = bf16_hi(v[0]); bb[fa][2] = bf16_lo(v[1]); bb[fa][3] = bf16_hi(v[1]);
-    } else {
-      bb[fa][0] = bb[fa][1] = bb[fa][2] = bb[fa][3] = 0.f;
-    }
-  }
-
+      for (int c = 0; c < 2; ++c) {
+        if (c == 0) {
 #pragma unroll
-  for (int tb = 0; tb < 8; ++tb) {
-    const int t = t0 + brow + 16 * tb + l16;
-    if (t >= T) continue;
-    int lo = 0, hi = batch - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (cu[mid] <= t) lo = mid;
-      else hi = mid - 1;
-    }
-    const int pos = plen[lo] + (t - cu[lo]);
-    int blk = 0, slot = 0;
-    if (kind != 0) {
-      blk = bt[int64_t(lo) * bt_stride + pos / kBs];
-      if (blk < 0 || blk >= num_blocks) continue;
-      slot = pos % kBs;
-    }
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const int j = j0 + 16 * p + 4 * g4;   // rotary index of element 0
-      float o0[4], o1[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o0[e] = acc[p][tb][e] + bb[p][e];
-        o1[e] = acc[p + 2][tb][e] + bb[p + 2][e];
-      }
-      if (kind != 2) {
-        const float* cs = rope + (int64_t(pos) * (D / 2) + j) * 2;
-        const f32x4 c01 = *reinterpret_cast<const f32x4*>(cs);
-        const f32x4 c23 = *reinterpret_cast<const f32x4*>(cs + 4);
-        const float c[4] = {c01[0], c01[2], c23[0], c23[2]};
-        const float sn[4] = {c01[1], c01[3], c23[1], c23[3]};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float av = o0[e], bv = o1[e];
-          o0[e] = av * c[e] - bv * sn[e];
-          o1[e] = bv * c[e] + av * sn[e];
+          for (int fa = 0; fa < 4; ++fa) {
+            af[0][fa] = ld(wst + arow(fa) * kRow + so0);
+            af[1][fa] = ld(wst + arow(fa) * kRow + so1);
+          }
         }
+#pragma unroll
+        for (int tb = 0; tb < 8; ++tb) bx[tb] = ld(xst + (brow + 16 * tb) * kRow + (c ? so1 : so0));
+        if (c == 0) {
+          issue4(c_w, offw, s4);
+        } else {
+          issue4(c_x, offx, slot);
+          cursor_next();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (c == 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+        else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(8));
+        interval_barrier();
+        __builtin_amdgcn_s_setprio(1);
+        if (!(half_last && k == nk - 1 && c == 0)) {
+#pragma unroll
+          for (int tb = 0; tb < 8; ++tb)
+#pragma unroll
+            for (int fa = 0; fa < 4; ++fa)
+              acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[c][fa], bx[tb], acc[fa][tb], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        interval_barrier();
       }
-      if (kind == 0) {
-        uint16_t* qp = q_out + (int64_t(t) * hq + hf) * D + j;
-        *reinterpret_cast<u32x2*>(qp) = u32x2{pack_bf16x2(o0[0], o0[1]), pack_bf16x2(o0[2], o0[3])};
-        *reinterpret_cast<u32x2*>(qp + D / 2) = u32x2{pack_bf16x2(o1[0], o1[1]), pack_bf16x2(o1[2], o1[3])};
-      } else {
-        // k or v: row `slot` of the (block, head) in its cache, [blk][g][slot][d]
-        uint16_t* cp = (kind == 1 ? k_cache : v_cache) + ((int64_t(blk) * hkv + g) * kBs + slot) * D + j;
-        *reinterpret_cast<u32x2*>(cp) = u32x2{pack_bf16x2(o0[0], o0[1]), pack_bf16x2(o0[2], o0[3])};
-        *reinterpret_cast<u32x2*>(cp + D / 2) = u32x2{pack_bf16x2(o1[0], o1[1]), pack_bf16x2(o1[2], o1[3])};
-      }
+      free_slot = sx;
+      slot = s2;
     }
+    // ---- epilogue. The slot of the last step's x rows is free until the next
+    // tile's first step, whose copies into a wave's part of it are that wave's.
+    int f0, t0;
+    tile_origin(a, tile, kTileF, kTileT, f0, t0);
+    const int hf = min(f0, f_max) / D + head_l;
+    if (hf * D >= f0)
+      store_results<D, 2, 8>(a, acc, hf, j0, min(t0, t_max) + brow, t0, lds + free_slot * kSlot + wave * kOwn, lane);
+    clear();
   }
+  if (wt == 0) interval_barrier();
+  // the copies past the last tile must not outlive the workgroup's LDS
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
 }
 
 cw_status check_launch(const char* what) {
@@ -358,20 +509,33 @@ extern "C" cw_status cw_qkv_rope_append(const void* x, const void* w, const void
   const int64_t per_xcd = (n_ftiles * n_ttiles + cw::kNumXcd - 1) / cw::kNumXcd;
   if (per_xcd * cw::kNumXcd > INT32_MAX) return cw::fail(CW_EUNSUPPORTED, std::string(what) + ": too many tiles");
   auto* s = static_cast<hipStream_t>(stream);
-  const dim3 grid(unsigned(per_xcd * cw::kNumXcd));
-  auto* xp = static_cast<const uint8_t*>(x);
-  auto* wp = static_cast<const uint8_t*>(w);
-  auto* bp = static_cast<const uint16_t*>(bias);
-  auto* qp = static_cast<uint16_t*>(q_out);
-  auto* kp = static_cast<uint16_t*>(k_cache);
-  auto* vp = static_cast<uint16_t*>(v_cache);
+  // one persistent workgroup per CU
+  const dim3 grid(unsigned(std::min<int64_t>(per_xcd, cw::kNumCu / cw::kNumXcd) * cw::kNumXcd));
+  QkvArgs a;
+  a.x = static_cast<const uint8_t*>(x);
+  a.w = static_cast<const uint8_t*>(w);
+  a.bias = static_cast<const uint16_t*>(bias);
+  a.rope = rope;
+  a.q_out = static_cast<uint16_t*>(q_out);
+  a.k_cache = static_cast<uint16_t*>(k_cache);
+  a.v_cache = static_cast<uint16_t*>(v_cache);
+  a.bt = block_table;
+  a.cu = cu_suffix_dev;
+  a.plen = prefix_len_dev;
+  a.T = int(rows);
+  a.hidden = hidden;
+  a.n_feat = int(n_feat);
+  a.bt_stride = bt_stride;
+  a.batch = batch;
+  a.hq = num_q_heads;
+  a.hkv = num_kv_heads;
+  a.num_blocks = num_blocks;
+  a.n_ftiles = int(n_ftiles);
+  a.n_ttiles = int(n_ttiles);
+  a.per_xcd = int(per_xcd);
   if (head_dim == 128)
-    hipLaunchKernelGGL(qkv_rope_append_kernel<128>, grid, dim3(kThreads), 0, s, xp, wp, bp, rope, int(rows), hidden,
-                       int(n_feat), qp, kp, vp, block_table, bt_stride, cu_suffix_dev, prefix_len_dev, batch,
-                       num_q_heads, num_kv_heads, num_blocks, int(n_ftiles), int(n_ttiles), int(per_xcd));
+    hipLaunchKernelGGL(qkv_rope_append_kernel<128>, grid, dim3(kThreads), 0, s, a);
   else
-    hipLaunchKernelGGL(qkv_rope_append_kernel<64>, grid, dim3(kThreads), 0, s, xp, wp, bp, rope, int(rows), hidden,
-                       int(n_feat), qp, kp, vp, block_table, bt_stride, cu_suffix_dev, prefix_len_dev, batch,
-                       num_q_heads, num_kv_heads, num_blocks, int(n_ftiles), int(n_ttiles), int(per_xcd));
+    hipLaunchKernelGGL(qkv_rope_append_kernel<64>, grid, dim3(kThreads), 0, s, a);
   return check_launch("qkv_rope_append launch");
 }

@@ -235,3 +235,21 @@ def test_llama70b_long_sampled():
     c = Case(w.name, 64, 8, 128, 8192, s.block_table, s.cu_suffix, s.prefix_len, s.num_blocks, seed=13,
              bias=False)
     c.run().check_sampled()
+
+
+TILES = [
+    # one token and one feature tile moved back to the last row: 257 tokens, 3 heads of 128
+    ("edge-257x384", 1, 1, 128, 64, [0], [257], {}),
+    # exactly one tile, and one token short of it
+    ("edge-256x256", 2, 2, 64, 96, [16], [256], {}),
+    ("edge-255x640", 8, 1, 64, 160, [0, 48], [100, 155], {"bias": False}),
+    # more tiles than workgroups (24 x 12): the ring runs on across tiles, at one, two and three steps per tile
+    ("rounds-h32", 32, 8, 128, 32, [0, 32, 0], [1000, 1, 1999], {"bias": False}),
+    ("rounds-h96", 32, 8, 128, 96, [16, 0, 0, 0], [1500, 0, 1300, 141], {}),
+    ("rounds-h192", 32, 8, 128, 192, [0], [2900], {}),
+]
+
+
+@pytest.mark.parametrize("name,hq,hkv,D,hidden,plen,slen,kw", TILES, ids=[c[0] for c in TILES])
+def test_tile_edges_and_rounds(name, hq, hkv, D, hidden, plen, slen, kw):
+    _ragged(name, hq, hkv, D, hidden, plen, slen, seed=21, **kw).run().check_full()
