@@ -12,8 +12,9 @@
 //   q -> q_out [T, Hq, D];  k -> K cache [blk][g][slot][d];
 //   v -> V cache [blk][g][slot][d]
 //
-// Design (persistent workgroups of 8 wavefronts, one per CU, walking tiles of
-// 256 features x 256 tokens):
+// Eight tile shapes serve batches from one token to tens of thousands (kShapes:
+// which, and why). The largest, persistent workgroups of 8 wavefronts, one per
+// CU, walking tiles of 256 features x 256 tokens:
 //  * The product is formed as C^T = W x^T with v_mfma_f32_16x16x32_bf16:
 //    A = 16 rows of W, B = 16 token rows of x, 32 hidden per instruction. In
 //    the 16x16 accumulator a lane holds one token and 4 consecutive features,
@@ -46,6 +47,7 @@
 //    run together on one L2 share their W and x rows.
 //  * fp32 accumulation; bias, rotation (fp32 cos/sin from a table the host
 //    computes in fp64) and one bf16 rounding in the epilogue.
+// Smaller tiles (below) keep this staging, operand layout and epilogue.
 // Bound: the matrix pipe under the card's power limit (the clock falls to about
 // 1.7 GHz on random data, 2.39 on zeros). T = 16,128, hidden 4,096, 6,144
 // features (812 GFLOP): 579 us, 1.40 PFLOP/s; with one barrier per step for all
@@ -463,10 +465,401 @@ void qkv_rope_append_kernel(const QkvArgs a) {
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
 }
 
+// ---------------------------------------------------------------------------
+// Fewer tokens: one smaller tile per workgroup, so that more CUs work on the
+// batch. Same staging, operand layout and alternation of two wave groups as
+// above, with one reading and one product interval (both k-steps) per step.
+//  * KSPLIT false: 256 features x 128 tokens. Wave (wf, group) owns 64 features
+//    and 64 tokens. A ring of three stages (W and x rows of a step).
+//  * KSPLIT true: 128 features x 128 tokens; the groups share the tile and take
+//    alternate steps of 64 hidden, each with a five-slot ring of its own, and
+//    add their sums at the end (each group finishes half of the tokens).
+// ---------------------------------------------------------------------------
+template <bool KSPLIT>
+struct TileGeom {
+  static constexpr int TF = KSPLIT ? 128 : 256, TT = 128;
+  static constexpr int W_BYTES = TF * kRow, X_BYTES = TT * kRow;
+  static constexpr int RING = KSPLIT ? 5 * W_BYTES : 3 * (W_BYTES + X_BYTES);   // per group / shared
+  static constexpr int LDS = KSPLIT ? 2 * RING : RING;
+  static constexpr int EXCHANGE = 8 * 8192;   // KSPLIT: the sums handed to the other group
+  static_assert(!KSPLIT || W_BYTES == X_BYTES, "slots hold W and x rows in turn");
+  static_assert(LDS <= 160 * 1024 && EXCHANGE + 8 * 4096 <= LDS, "LDS of one CU");
+};
+
+template <int D, bool KSPLIT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void qkv_tile_kernel(const QkvArgs a) {
+  using G = TileGeom<KSPLIT>;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  const int tile = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+  if (tile >= a.n_ftiles * a.n_ttiles) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w4 = wave & 3, gr = wave >> 2;
+
+  int f_own, t_own;
+  tile_origin(a, tile, G::TF, G::TT, f_own, t_own);
+  // (a tile past the last row of W or x is moved back, as above)
+  const int f0 = min(f_own, max(a.n_feat - G::TF, 0)), t0 = min(t_own, max(a.T - G::TT, 0));
+
+  // ---- staging: planes of 64 hidden, one per step (KSPLIT: per step and group)
+  const int64_t hb = int64_t(a.hidden) * 2;
+  const int planes = (a.hidden + kStep - 1) / kStep;
+  const int nk = KSPLIT ? (planes + 1) / 2 : planes;
+  const bool half_last = (a.hidden % kStep) != 0;
+  const uint8_t* const wb = a.w + int64_t(f0) * hb;
+  const uint8_t* const xb = a.x + int64_t(t0) * hb;
+  constexpr int NX = KSPLIT ? 4 : 2;             // x copies per wave and step
+  const int rw0 = KSPLIT ? 32 * w4 : 32 * wave;  // this wave's W and x rows
+  const int rx0 = KSPLIT ? 32 * w4 : 16 * wave;
+  uint32_t offw[4], offx[NX];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = rw0 + 8 * i + (lane >> 3);
+    int c = ((lane & 7) ^ row_swz(row)) * 16;
+    if (a.hidden < kStep) c &= ~64;
+    offw[i] = uint32_t(min(staged_feature(row), a.n_feat - 1)) * uint32_t(hb) + c;
+  }
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    const int row = rx0 + 8 * i + (lane >> 3);
+    int c = ((lane & 7) ^ row_swz(row)) * 16;
+    if (a.hidden < kStep) c &= ~64;
+    offx[i] = uint32_t(min(row, a.T - 1)) * uint32_t(hb) + c;
+  }
+  auto plane_of = [&](int s) { return KSPLIT ? 2 * s + gr : s; };
+  // byte offset in a row of step s (past the last plane: that plane again, which nothing reads)
+  auto step_off = [&](int s) __attribute__((always_inline)) -> int64_t {
+    const int p = min(plane_of(s), planes - 1);
+    return int64_t(p) * kRow - ((half_last && p == planes - 1 && p > 0) ? kRow / 2 : 0);
+  };
+  auto issue_w = [&](int s, uint32_t dst) __attribute__((always_inline)) {
+    const uint8_t* base = wb + step_off(s);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) copy16_to_lds(base, offw[i], dst + (rw0 + 8 * i) * kRow);
+  };
+  auto issue_x = [&](int s, uint32_t dst) __attribute__((always_inline)) {
+    const uint8_t* base = xb + step_off(s);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) copy16_to_lds(base, offx[i], dst + (rx0 + 8 * i) * kRow);
+  };
+
+  // ---- operand rows of this wave
+  constexpr int kWavesPerHead = D / 64;
+  const int wf = KSPLIT ? (w4 & 1) : w4;
+  const int head_l = wf / kWavesPerHead;
+  const int j0 = (wf % kWavesPerHead) * 32;
+  const int arow0 = head_l * D + j0;
+  const int brow = 64 * (KSPLIT ? (w4 >> 1) : gr);
+  const int l16 = lane & 15;
+  const int g4 = lane >> 4;
+  const int so[2] = {l16 * kRow + ((g4 ^ row_swz(l16)) << 4), l16 * kRow + (((4 + g4) ^ row_swz(l16)) << 4)};
+  auto ld = [&](int addr) __attribute__((always_inline)) -> bf16x8 {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + addr));
+  };
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int fa = 0; fa < 4; ++fa)
+#pragma unroll
+    for (int tb = 0; tb < 4; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // Ring positions of the W and x rows of a step. KSPLIT: slots 2 s % 5 and
+  // (2 s + 1) % 5 of the group's ring, walked by `slot`; else stage s % 3.
+  // Group 0 reads step s in interval 2 s, group 1 in 2 s + 1:
+  //  - KSPLIT (a group's ring is its own): W of step s + 2 goes into the slot of
+  //    x of step s - 1 when the group reads step s; x of step s + 2 into the
+  //    slot of W of step s once the barrier after that reading is passed. A
+  //    wave's copies of step s + 1 have landed at the end of its products.
+  //  - else: step s + 2 goes into the stage of step s - 1, last read (by group
+  //    1) in interval 2 s - 1, when a group reads step s; a wave's copies of
+  //    step s + 1 have landed at the end of interval 2 s + 1.
+  const int ring0 = KSPLIT ? gr * G::RING : 0;
+  int slot = 0;
+  auto adv = [](int v, int d) { return v + d >= 5 ? v + d - 5 : v + d; };
+  auto w_pos = [&](int s, int sl) { return KSPLIT ? ring0 + sl * G::W_BYTES : (s % 3) * (G::W_BYTES + G::X_BYTES); };
+  auto x_pos = [&](int s, int sl) {
+    return KSPLIT ? ring0 + adv(sl, 1) * G::W_BYTES : (s % 3) * (G::W_BYTES + G::X_BYTES) + G::W_BYTES;
+  };
+  constexpr int kFly = 4 + NX;   // copies of one step
+  issue_w(0, lds0 + w_pos(0, 0));
+  issue_x(0, lds0 + x_pos(0, 0));
+  issue_w(1, lds0 + w_pos(1, 2));
+  issue_x(1, lds0 + x_pos(1, 2));
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
+  interval_barrier();
+  if (gr == 1) interval_barrier();
+  int stage = 0;
+  for (int s = 0; s < nk; ++s) {
+    const int wst = KSPLIT ? w_pos(s, slot) : stage * (G::W_BYTES + G::X_BYTES);
+    const int xst = KSPLIT ? x_pos(s, slot) : wst + G::W_BYTES;
+    bf16x8 af[2][4], bx[2][4];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int fa = 0; fa < 4; ++fa)
+        af[ks][fa] = ld(wst + (arow0 + (fa >> 1) * (D / 2) + (fa & 1) * 16) * kRow + so[ks]);
+#pragma unroll
+      for (int tb = 0; tb < 4; ++tb) bx[ks][tb] = ld(xst + (brow + 16 * tb) * kRow + so[ks]);
+    }
+    if constexpr (KSPLIT) {
+      issue_w(s + 2, lds0 + ring0 + adv(slot, 4) * G::W_BYTES);
+    } else {
+      const uint32_t nst = (stage == 0 ? 2 : stage - 1) * (G::W_BYTES + G::X_BYTES);
+      issue_w(s + 2, lds0 + nst);
+      issue_x(s + 2, lds0 + nst + G::W_BYTES);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (!KSPLIT && gr == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+    interval_barrier();
+    if constexpr (KSPLIT) issue_x(s + 2, lds0 + ring0 + slot * G::W_BYTES);
+    __builtin_amdgcn_s_setprio(1);
+    const int p = plane_of(s);
+    const bool half = half_last && p == planes - 1;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      if (p < planes && !(half && ks == 0)) {
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+          for (int fa = 0; fa < 4; ++fa)
+            acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][fa], bx[ks][tb], acc[fa][tb], 0, 0, 0);
+      }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (KSPLIT || gr == 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
+    interval_barrier();
+    slot = adv(slot, 2);
+    stage = stage == 2 ? 0 : stage + 1;
+  }
+  if (gr == 0) interval_barrier();
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  interval_barrier();   // every wave's copies have landed: the ring is free
+
+  const int hf = f0 / D + head_l;
+  const bool mine = hf * D >= f_own;
+  if constexpr (KSPLIT) {
+    // Group 0 keeps token blocks 0 and 1, group 1 blocks 2 and 3; the other two
+    // go to the other group's wave of the same features and tokens.
+    f32x4 sum[4][2];
+#pragma unroll
+    for (int fa = 0; fa < 4; ++fa)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const f32x4 give = gr ? acc[fa][i] : acc[fa][2 + i];
+        sum[fa][i] = gr ? acc[fa][2 + i] : acc[fa][i];
+        *reinterpret_cast<f32x4*>(lds + wave * 8192 + (fa * 2 + i) * 1024 + lane * 16) = give;
+      }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+    interval_barrier();
+#pragma unroll
+    for (int fa = 0; fa < 4; ++fa)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        sum[fa][i] += *reinterpret_cast<const f32x4*>(lds + (wave ^ 4) * 8192 + (fa * 2 + i) * 1024 + lane * 16);
+    if (mine)
+      store_results<D, 2, 2>(a, sum, hf, j0, t0 + brow + 32 * gr, t_own, lds + G::EXCHANGE + wave * 4096, lane);
+  } else {
+    if (mine) store_results<D, 2, 4>(a, acc, hf, j0, t0 + brow, t_own, lds + wave * 4096, lane);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Fewest tokens: a workgroup takes 16 FH rotary pairs (2 x 16 FH rows of W) and
+// 16 TB tokens and streams its rows through a ring of ST stages of PL planes
+// (64 hidden each). The waves split a stage by k-step (KW = 2 PL) and, where
+// that leaves waves over, by token blocks; their sums are added at the end.
+// Bound by the read of W: the ring keeps ST - 1 stages (up to 128 KB) in flight
+// per CU, and the products hide under it.
+// ---------------------------------------------------------------------------
+template <int FH, int TB, int PL, int ST>
+struct StreamGeom {
+  static constexpr int TF = 32 * FH, TT = 16 * TB, ROWS = TF + TT;
+  static constexpr int KW = 2 * PL, TW = 8 / KW, NB = TB / TW;   // waves over k-steps and tokens; blocks per wave
+  static constexpr int PLANE = ROWS * kRow, STAGE = PL * PLANE;
+  static constexpr int COPIES = STAGE / 1024, NC = COPIES / 8;   // 8-row copies per stage, per wave
+  static constexpr int FB = 2 * FH;
+  static constexpr int SUMS = 8 * FB * NB * 1024;
+  static constexpr int TAIL = SUMS + TB * FH * 2048;   // sums and cos/sin rows, after the ring is done
+  static constexpr int LDS = ST * STAGE > TAIL ? ST * STAGE : TAIL;
+  static_assert(COPIES % 8 == 0 && TW * NB == TB, "even shares");
+  static_assert(LDS <= 160 * 1024, "LDS of one CU");
+};
+
+template <int D, int FH, int TB, int PL, int ST>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void qkv_stream_kernel(const QkvArgs a) {
+  using G = StreamGeom<FH, TB, PL, ST>;
+  constexpr int FB = G::FB, NB = G::NB, NC = G::NC;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  const int tile = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+  if (tile >= a.n_ftiles * a.n_ttiles) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  constexpr int kUnits = D / G::TF;   // tiles per head
+  int ft, t0;
+  tile_origin(a, tile, 1, G::TT, ft, t0);
+  const int hf = ft / kUnits, j0 = (ft % kUnits) * (16 * FH);
+
+  const int64_t hb = int64_t(a.hidden) * 2;
+  const int planes = (a.hidden + kStep - 1) / kStep;
+  const int nk = (planes + PL - 1) / PL;
+  const bool half_last = (a.hidden % kStep) != 0;
+  // Copy i of this wave: rows 8 (c % (ROWS / 8)) .. + 7 of plane c / (ROWS / 8),
+  // c = wave + 8 i; W rows of the two halves of the pairs first, then x rows.
+  const uint8_t* base[NC];
+  uint32_t off[NC];
+  int pl[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = wave + 8 * i;
+    pl[i] = c / (G::ROWS / 8);
+    const int r8 = 8 * (c % (G::ROWS / 8));
+    const int row = r8 + (lane >> 3);
+    int ch = ((lane & 7) ^ row_swz(row)) * 16;
+    if (a.hidden < kStep) ch &= ~64;
+    if (r8 < G::TF) {
+      const int half = row / (16 * FH), r = row % (16 * FH);
+      base[i] = a.w + (int64_t(hf) * D + j0) * hb;
+      off[i] = uint32_t(half * (D / 2) + (FH == 2 ? staged_feature(r) : r)) * uint32_t(hb) + ch;
+    } else {
+      base[i] = a.x + int64_t(t0) * hb;
+      off[i] = uint32_t(min(row - G::TF, a.T - 1 - t0)) * uint32_t(hb) + ch;
+    }
+  }
+  auto issue = [&](int s, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      // (past the last plane: that plane again, which nothing uses)
+      const int p = min(PL * s + pl[i], planes - 1);
+      const int64_t o = int64_t(p) * kRow - ((half_last && p == planes - 1 && p > 0) ? kRow / 2 : 0);
+      copy16_to_lds(base[i] + o, off[i], lds0 + stage * G::STAGE + (wave + 8 * i) * 1024);
+    }
+  };
+
+  const int u = wave % G::KW, tw = wave / G::KW;   // this wave's k-step of a stage and token share
+  const int so = l16 * kRow + ((((u & 1) * 4 + g4) ^ row_swz(l16)) << 4) + (u >> 1) * G::PLANE;
+  f32x4 acc[FB][NB];
+#pragma unroll
+  for (int fa = 0; fa < FB; ++fa)
+#pragma unroll
+    for (int tb = 0; tb < NB; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int s, int stage) __attribute__((always_inline)) {
+    const int p = PL * s + (u >> 1);
+    if (p >= planes || (half_last && p == planes - 1 && (u & 1) == 0)) return;
+    const uint8_t* st = lds + stage * G::STAGE + so;
+    bf16x8 af[FB], bx[NB];
+#pragma unroll
+    for (int fa = 0; fa < FB; ++fa) af[fa] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + 16 * fa * kRow));
+#pragma unroll
+    for (int tb = 0; tb < NB; ++tb)
+      bx[tb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + (G::TF + (tw * NB + tb) * 16) * kRow));
+#pragma unroll
+    for (int fa = 0; fa < FB; ++fa)
+#pragma unroll
+      for (int tb = 0; tb < NB; ++tb)
+        acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[fa], bx[tb], acc[fa][tb], 0, 0, 0);
+  };
+  // Stage s % ST holds step s. At the barrier of step s every wave's copies of
+  // step s have landed (ST - 2 younger steps stay in flight) and every wave's
+  // reads of step s - 1 are complete, so step s + ST - 1 goes into its stage.
+#pragma unroll
+  for (int i = 0; i < ST - 1; ++i)
+    if (i < nk) issue(i, i);
+  int stage = 0, s = 0;
+  for (; s + ST - 1 < nk; ++s) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(NC * (ST - 2)));
+    interval_barrier();
+    issue(s + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+    compute(s, stage);
+    stage = stage == ST - 1 ? 0 : stage + 1;
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  interval_barrier();
+  for (; s < nk; ++s) {   // the last steps are all there
+    compute(s, stage);
+    stage = stage == ST - 1 ? 0 : stage + 1;
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  interval_barrier();   // every wave is done with the ring
+  // ---- add the waves' sums: wave tb finishes token block tb
+#pragma unroll
+  for (int fa = 0; fa < FB; ++fa)
+#pragma unroll
+    for (int tb = 0; tb < NB; ++tb)
+      *reinterpret_cast<f32x4*>(lds + ((wave * NB + tb) * FB + fa) * 1024 + lane * 16) = acc[fa][tb];
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+  interval_barrier();
+  if (wave >= TB) return;
+  f32x4 sum[FB][1];
+#pragma unroll
+  for (int fa = 0; fa < FB; ++fa) {
+    sum[fa][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < G::KW; ++v)
+      sum[fa][0] += *reinterpret_cast<const f32x4*>(
+          lds + ((((wave / NB) * G::KW + v) * NB + wave % NB) * FB + fa) * 1024 + lane * 16);
+  }
+  const int tfirst = t0 + 16 * wave;
+  store_results<D, FH, 1>(a, sum, hf, j0, tfirst, tfirst, lds + G::SUMS + wave * FH * 2048, lane);
+}
+
 cw_status check_launch(const char* what) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return cw::fail(CW_EHIP, std::string(what) + ": " + hipGetErrorString(e));
   return cw::ok();
+}
+
+// The tile shapes, and what a call costs with each: `tiles` tiles in rounds of
+// one per CU, a round fixed + planes * us (planes = hidden / 64), where us grows
+// from `light` (few CUs busy) to `full` (all busy). The shape with the smallest
+// estimate is taken. The constants are fits to calls measured back to back at
+// T = 1 .. 8,000 tokens, 384 .. 10,240 features and hidden 256 .. 8,192 (all
+// shapes at each size): the estimate's choice is within 3.2 % of the best shape
+// everywhere and 0.1 % on average. Leaving out any one shape costs 17 to 59 %
+// at its sizes (the 32 x 16 tile: 17 %). Examples, in us, 6,144 features and
+// hidden 4,096, 256 x 256 tile against the chosen one: T = 16: 66.4 / 10.9
+// (32 x 16); 64: 67.3 / 15.3 (32 x 64); 128: 68.3 / 20.0 (64 x 64); 256: 70.8 /
+// 27.0 (64 x 128); 576: 71.6 / 33.9 (128 x 128); 1,024: 72.3 / 52.0 (256 x 128);
+// 1,536: 75.8 (128 x 128: 93.3).
+struct QkvShape {
+  int tile_f, tile_t;
+  bool persistent;
+  double fixed, light, full;   // us
+  void (*kernel128)(QkvArgs);
+  void (*kernel64)(QkvArgs);
+};
+const QkvShape kShapes[] = {
+    {256, 256, true, 8.7, 0.90, 1.38, qkv_rope_append_kernel<128>, qkv_rope_append_kernel<64>},
+    {256, 128, false, 5.5, 0.565, 0.83, qkv_tile_kernel<128, false>, qkv_tile_kernel<64, false>},
+    {128, 128, false, 5.0, 0.325, 0.46, qkv_tile_kernel<128, true>, qkv_tile_kernel<64, true>},
+    {64, 128, false, 4.4, 0.34, 0.38, qkv_stream_kernel<128, 2, 8, 2, 3>, qkv_stream_kernel<64, 2, 8, 2, 3>},
+    {64, 64, false, 3.7, 0.242, 0.27, qkv_stream_kernel<128, 2, 4, 2, 5>, qkv_stream_kernel<64, 2, 4, 2, 5>},
+    {32, 64, false, 3.7, 0.173, 0.21, qkv_stream_kernel<128, 1, 4, 2, 6>, qkv_stream_kernel<64, 1, 4, 2, 6>},
+    {32, 32, false, 3.9, 0.104, 0.14, qkv_stream_kernel<128, 1, 2, 4, 5>, qkv_stream_kernel<64, 1, 2, 4, 5>},
+    {32, 16, false, 3.7, 0.100, 0.13, qkv_stream_kernel<128, 1, 1, 4, 6>, qkv_stream_kernel<64, 1, 1, 4, 6>},
+};
+
+const QkvShape& pick_shape(int64_t rows, int64_t n_feat, int64_t hidden) {
+  const double planes = double((hidden + kStep - 1) / kStep);
+  const QkvShape* best = nullptr;
+  double best_us = 0;
+  for (const QkvShape& s : kShapes) {
+    const int64_t tiles = ((n_feat + s.tile_f - 1) / s.tile_f) * ((rows + s.tile_t - 1) / s.tile_t);
+    const int64_t rounds = tiles / cw::kNumCu, rest = tiles % cw::kNumCu;
+    double us = double(rounds) * (s.fixed + planes * s.full);
+    if (rest > 0) us += s.fixed + planes * (s.light + (s.full - s.light) * double(rest) / cw::kNumCu);
+    if (!best || us < best_us) {
+      best = &s;
+      best_us = us;
+    }
+  }
+  return *best;
 }
 
 }  // namespace
@@ -504,13 +897,13 @@ extern "C" cw_status cw_qkv_rope_append(const void* x, const void* w, const void
   if (!x || !q_out) return cw::fail(CW_EINVAL, std::string(what) + ": x and q_out are required");
   if (rows > INT32_MAX - kTileT) return cw::fail(CW_EUNSUPPORTED, std::string(what) + ": too many suffix rows");
   const int64_t n_feat = int64_t(num_q_heads + 2 * num_kv_heads) * head_dim;
-  const int64_t n_ftiles = (n_feat + kTileF - 1) / kTileF;
-  const int64_t n_ttiles = (rows + kTileT - 1) / kTileT;
+  const QkvShape& sh = pick_shape(rows, n_feat, hidden);
+  const int64_t n_ftiles = (n_feat + sh.tile_f - 1) / sh.tile_f;
+  const int64_t n_ttiles = (rows + sh.tile_t - 1) / sh.tile_t;
   const int64_t per_xcd = (n_ftiles * n_ttiles + cw::kNumXcd - 1) / cw::kNumXcd;
   if (per_xcd * cw::kNumXcd > INT32_MAX) return cw::fail(CW_EUNSUPPORTED, std::string(what) + ": too many tiles");
   auto* s = static_cast<hipStream_t>(stream);
-  // one persistent workgroup per CU
-  const dim3 grid(unsigned(std::min<int64_t>(per_xcd, cw::kNumCu / cw::kNumXcd) * cw::kNumXcd));
+  const dim3 grid(unsigned((sh.persistent ? std::min<int64_t>(per_xcd, cw::kNumCu / cw::kNumXcd) : per_xcd) * cw::kNumXcd));
   QkvArgs a;
   a.x = static_cast<const uint8_t*>(x);
   a.w = static_cast<const uint8_t*>(w);
@@ -533,9 +926,6 @@ extern "C" cw_status cw_qkv_rope_append(const void* x, const void* w, const void
   a.n_ftiles = int(n_ftiles);
   a.n_ttiles = int(n_ttiles);
   a.per_xcd = int(per_xcd);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(qkv_rope_append_kernel<128>, grid, dim3(kThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL(qkv_rope_append_kernel<64>, grid, dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(head_dim == 128 ? sh.kernel128 : sh.kernel64, grid, dim3(kThreads), 0, s, a);
   return check_launch("qkv_rope_append launch");
 }

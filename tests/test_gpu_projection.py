@@ -237,16 +237,26 @@ def test_llama70b_long_sampled():
     c.run().check_sampled()
 
 
+
 TILES = [
-    # one token and one feature tile moved back to the last row: 257 tokens, 3 heads of 128
-    ("edge-257x384", 1, 1, 128, 64, [0], [257], {}),
-    # exactly one tile, and one token short of it
-    ("edge-256x256", 2, 2, 64, 96, [16], [256], {}),
-    ("edge-255x640", 8, 1, 64, 160, [0, 48], [100, 155], {"bias": False}),
-    # more tiles than workgroups (24 x 12): the ring runs on across tiles, at one, two and three steps per tile
-    ("rounds-h32", 32, 8, 128, 32, [0, 32, 0], [1000, 1, 1999], {"bias": False}),
-    ("rounds-h96", 32, 8, 128, 96, [16, 0, 0, 0], [1500, 0, 1300, 141], {}),
-    ("rounds-h192", 32, 8, 128, 192, [0], [2900], {}),
+    # (tile features x tokens the size selects) edges of tiles, odd and half steps of hidden, several rounds
+    ("32x16-one", 1, 1, 128, 96, [0], [1], {}),
+    ("32x16-two", 8, 2, 128, 1056, [16, 0], [9, 8], {"bias": False}),
+    ("32x16-d64", 2, 1, 64, 672, [0, 48], [15, 1], {}),
+    ("32x32", 28, 4, 128, 160, [0], [31], {}),
+    ("32x64", 28, 4, 128, 2080, [32], [33], {}),
+    ("32x64-d64", 28, 4, 64, 160, [0, 16, 0], [30, 0, 35], {"bias": False}),
+    ("64x64", 28, 4, 128, 1056, [0, 0], [64, 65], {}),
+    ("64x64-d64", 28, 4, 64, 1056, [16], [200], {}),
+    ("64x128", 28, 4, 128, 1056, [0, 48], [129, 171], {}),
+    ("64x128-d64", 28, 4, 64, 2080, [0], [500], {"bias": False}),
+    ("128x128", 28, 4, 128, 2080, [0, 16], [257, 190], {}),
+    ("128x128-d64", 28, 4, 64, 544, [0], [1100], {}),
+    ("256x128", 28, 4, 128, 544, [0, 32, 0], [700, 1, 499], {}),
+    ("256x128-rounds", 28, 4, 64, 1056, [0], [2100], {"bias": False}),
+    ("256x256", 28, 4, 128, 1056, [0, 0], [1025, 1075], {}),
+    # more tiles than workgroups: the ring runs on across tiles
+    ("256x256-rounds", 64, 16, 64, 544, [0, 16, 0, 0], [2500, 0, 1999, 2], {}),
 ]
 
 
