@@ -1290,6 +1290,709 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// The same attention for long entries (long_entries): the kernel above (same plan, staging,
+// operand layouts, softmax and order of every sum, so the same result bit for
+// bit) with the two waves of a SIMD alternating instead of interleaving matrix
+// and vector work in one stream.
+//
+// A step j of a wave takes two intervals, each ended by a workgroup barrier:
+//   softmax(j):   row maximum, 2^S(j) packed to bf16 (VALU), copies
+//   products(j):  O^T += V(j)^T P(j)^T, then S(j+1) = K(j+1) Q^T   (MFMA)
+// The steps of all entries of a queue form one stream: after an entry's last
+// step S(j+1) is the next entry's first, so only the output and the change of
+// queries come between two entries. Waves 4-7 (group 1) run one interval behind
+// waves 0-3, so of the two waves of a SIMD one issues MFMAs back to back (1,045
+// cycles for 32, 1,024 at the pipe's rate) while the other does its softmax and
+// copies; with both kinds of work of every wave interleaved in one stream the
+// pair took about 3,340 cycles a step, against 2,850 now. What bounds it is the
+// softmax interval (about 1,400 cycles: while an MFMA reads its operands the
+// SIMD's vector issue is blocked) and the card's power limit: the clock follows
+// the matrix rate (1.75 GHz on the long batches), so variants that shorten the
+// stalls alone (copies spread over the interval or staggered by wave, scalar
+// cursor work moved under the products, deeper operand read-ahead) measured
+// within 1 %. Vector work put between the products delays them (row sums and
+// maxima there: 1,405 cycles for the 32).
+// Measured, both kernels in turn on one card (us, before / now): 8 x 5,248 tokens
+// 60 % cached 1,017 / 975; 8 x 10,368 tokens, 64 query heads 6,026 / 5,685;
+// 16-request trace batch 246 / 245.
+//
+// Ring hazards. Let step s be computed from ring position s % 4; products(s)
+// reads V(s) and K(s+1). Group 0 copies step s + 2 in softmax(s): the position
+// held step s - 2, last read by group 1 in its products(s-2), before group 0's
+// products(s-1). Group 1 copies step s + 3 in softmax(s): the position held step
+// s - 1, which both groups have read (group 0 is in products(s)). K(s+1) is
+// complete for group 0's products(s): group 0's copies of it were made in its
+// softmax(s-1) and are waited for at the end of softmax(s); group 1's were made
+// in its softmax(s-2) and are waited for at the end of its products(s-1), which
+// runs beside group 0's softmax(s).
+// ---------------------------------------------------------------------------
+template <int D, bool FUSED>
+__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void suffix_prefill_stream_kernel(const AttnArgs a) {
+  using G = AttnGeom<D>;
+  constexpr int KS = G::KS, DT = G::DT, RB = G::RB, LPW = G::LPW;
+  constexpr int KTILE = G::KTILE, BLK = G::BLK, VTILE = G::VTILE, KREG = G::KREG;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+
+  cint32_t* plan = reinterpret_cast<cint32_t*>(reinterpret_cast<uintptr_t>(a.plan));
+  // A plan whose header does not carry the fingerprint of the batch the host
+  // validated is not this batch's plan: compute nothing.
+  if (uint32_t(plan[cw::kHdrFpLo]) != a.fp_lo || uint32_t(plan[cw::kHdrFpHi]) != a.fp_hi) return;
+  const int32_t* const ents = a.plan + kPlanHeader;
+  const int grid = int(gridDim.x);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int l32 = lane & 31;
+  const int half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // ---- staging role of this wave: tensor (K or V) of block slot bs of a step
+  const int bs = wave >> 1;
+  const bool is_v = (wave & 1) != 0;
+  const uint8_t* const cache = reinterpret_cast<const uint8_t*>(is_v ? a.vc : a.kc);
+  // bytes from one physical block of a tensor to the next (below 2^28: the
+  // host refuses more than kMaxKvHeads KV heads), multiplied by a block ID as
+  // two 32-bit values
+  const uint32_t blk_bytes = uint32_t(a.hkv) * (kBs * RB);
+  // Per-lane source offset inside a block and LDS destination of copy i
+  // (relative to the wave's block slot in a stage; lane l lands at +16 l).
+  // Both tensors are staged chunk-major: 16-byte chunk c of key row r of a
+  // block at c 256 + r' 16, with r' = r for K and r' = r ^ 4 (c % 4) for V, so
+  // copy i (chunks 4 i .. 4 i + 3) brings lane l the chunk 4 i + l / 16 of key
+  // ckey (below).
+  // ckey (below). Copy i adds 64 i (its immediate offset) to the lane's base:
+  // off_c for a cache block (rows RB apart), off_n for rows of k_new / v_new
+  // (rows Hkv RB apart).
+  const int ckey = is_v ? ((lane & 15) ^ ((lane >> 4) << 2)) : (lane & 15);
+  const uint32_t off_c = uint32_t(ckey * RB + ((lane >> 4) << 4));
+  const uint32_t row_bytes = uint32_t(a.hkv) * RB;   // FUSED: from one k_new row to the next
+  const uint32_t off_n = FUSED ? uint32_t(ckey) * row_bytes + uint32_t((lane >> 4) << 4) : 0u;
+  const uint8_t* const fresh_base = reinterpret_cast<const uint8_t*>(is_v ? a.vn : a.kn);
+  // FUSED: largest source index of a whole block: cache blocks (16 b) and
+  // k_new / v_new rows (the host refuses pools of 2^27 blocks or more)
+  const int cache_lim = 16 * a.num_blocks - 16;
+  const int fresh_lim = a.total_rows - 16;
+  // table words per logical block
+  constexpr int TW = FUSED ? 2 : 1;
+  // LDS address of this wave's block slot in ring position 0
+  const uint32_t slot0 = lds0 + (is_v ? KREG + bs * BLK : bs * kBs * RB);
+  const uint32_t stage_stride = is_v ? VTILE : KTILE;
+  // This wave's area after the ring: output staging, and the target of loads
+  // whose data nothing reads.
+  const uint32_t own_area = lds0 + G::RING + wave * G::STAGING;
+
+  // ---- copy cursor: the entry and step whose blocks this wave copies next.
+  // Its state is wave-uniform. The words of the next entry the cursor enters
+  // are prefetched into cdesc (lane l holds word l % 16), loaded when the
+  // cursor enters the entry before it, so that a step that moves the cursor to
+  // a new entry waits for no load.
+  int ce = blockIdx.x;   // index of the entry whose words are in cdesc
+  int c_left = 0;        // steps of the cursor's entry not yet issued
+  int c_lb = 0;          // this wave's logical block at the cursor's step
+  int c_whole = 0;       // logical blocks below this hold 16 keys of the prompt
+  int c_last = 0;        // last logical block inside the prompt
+  int c_L = 0;           // prompt length of the cursor's request
+  int c_fast = 0;        // steps from the cursor's step that take the fast path of issue()
+  cint32_t* const bt = reinterpret_cast<cint32_t*>(reinterpret_cast<uintptr_t>(a.bt));
+  cint32_t* c_row = bt;   // block-table row of the cursor's request
+  cint32_t* c_ptr = bt;   // table word of this wave's block at the cursor's step
+  const uint8_t* c_src = cache;  // this wave's tensor at the cursor's KV head
+  int64_t c_delta = 0;   // FUSED: from c_src to this wave's tensor at that head in k_new / v_new
+  bool cdone = false;
+  auto entry_word_addr = [&](int e) __attribute__((always_inline)) -> const int32_t* {
+    return ents + int64_t(min(e, a.num_entries - 1)) * kEntryWords + (lane & 15);
+  };
+  int32_t cdesc = load_word_untracked(entry_word_addr(ce));
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(cdesc) :: "memory");
+  // Makes the entry whose words are in cdesc the cursor's entry and loads the
+  // words of the one after it; ends the cursor at the end of the queue or at
+  // an entry not written for this batch.
+  auto cursor_take = [&]() __attribute__((always_inline)) {
+    // (loaded before the last step's copies)
+    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(cdesc) : "n"(LPW) : "memory");
+    if (ce >= a.num_entries) { cdone = true; return; }
+    const int r = __builtin_amdgcn_readlane(cdesc, cw::kEntR);
+    const uint32_t tag = uint32_t(__builtin_amdgcn_readlane(cdesc, cw::kEntCheck));
+    if (r < 0 || tag != cw::entry_tag(a.fp_lo, a.fp_hi, uint32_t(ce))) { cdone = true; return; }
+    const int kb = __builtin_amdgcn_readlane(cdesc, cw::kEntKbeg);
+    c_left = __builtin_amdgcn_readlane(cdesc, cw::kEntKend) - kb;
+    c_lb = kb * (kKv / kBs) + bs;
+    c_L = __builtin_amdgcn_readlane(cdesc, cw::kEntL);
+    c_whole = c_L / kBs;
+    c_last = (c_L + kBs - 1) / kBs - 1;
+    c_row = bt + int64_t(r) * a.bt_stride * TW;
+    c_ptr = c_row + c_lb * TW;
+    const int cg = __builtin_amdgcn_readlane(cdesc, cw::kEntG);
+    c_src = cache + int64_t(cg) * (kBs * RB);
+    if constexpr (FUSED) c_delta = (fresh_base + int64_t(cg) * RB) - c_src;
+    // Fast steps: not the entry's last (whose issue() enters the next entry),
+    // the block whole (lb < c_whole) and the next step's table word inside
+    // the prompt's blocks (lb + 4 <= c_last), so that it needs no clamp.
+    const int lim = min(c_whole, c_last - (kKv / kBs - 1));
+    c_fast = min(c_left - 1, max(0, (lim - c_lb + kKv / kBs - 1) / (kKv / kBs)));
+    ce += grid;
+    cdesc = load_word_untracked(entry_word_addr(ce));
+  };
+  // Block-table word (FUSED: the table's pair) of this wave's block at the
+  // cursor's step, a scalar load made a step before its use. The index is
+  // clamped into the prompt. Past the last entry a harmless word (the plan's
+  // first) is loaded.
+  int bword0 = 0, bword1 = 0;
+  cint32_t* bw_ptr = plan;
+  auto load_bword = [&]() __attribute__((always_inline)) {
+    bword0 = bw_ptr[0];
+    if constexpr (FUSED) bword1 = bw_ptr[1];
+  };
+  auto cursor_load = [&]() __attribute__((always_inline)) {
+    c_ptr = c_row + min(c_lb, c_last) * TW;
+    bw_ptr = cdone ? plan : c_ptr;
+  };
+  // FUSED: the destination word of the block each ring position holds (lane
+  // p % 4), recorded when the block is copied, -1 when nothing is written.
+  int32_t dring = -1;
+  cursor_take();
+  cursor_load();
+  load_bword();
+  // prepare(pp) takes the cursor's step for ring position pp and advances the
+  // cursor; issue(pp) also copies the step. Every step makes LPW copies: where
+  // there is nothing to copy, or a block is not whole (it is staged through
+  // registers and waited for at once), they bring bytes of block 0 to this
+  // wave's own area, which nothing reads. So a wait for all but LPW operations
+  // always covers what was issued before a step's copies.
+  const uint8_t* cp_src = cache;
+  uint32_t cp_dst = own_area, cp_stride = 0, cp_off = off_c;
+  int cp_keys = -1;   // >= 0: a block to stage through registers, with so many valid keys
+  uint32_t cp_slot = 0, cp_poff = 0;
+  const uint8_t* cp_psrc = cache;
+  auto prepare = [&](int pp) __attribute__((always_inline)) {
+    const int raw = bword0, dword = FUSED ? bword1 : -1;
+    const int ring = pp & (kStages - 1);
+    const uint32_t dst = slot0 + uint32_t(ring) * stage_stride;
+    // The block's source: cache block raw; FUSED: the word is 16 b for cache
+    // block b, or 0x80000000 | R for rows R .. R + 15 of k_new / v_new, both
+    // scaled by row_bytes (selects by masks of the word's sign: the compiler
+    // keeps them scalar). `inb`: a whole block there lies inside its tensor.
+    const int sgn = FUSED ? raw >> 31 : 0;   // -1 for rows of k_new / v_new, else 0
+    const bool neg = sgn != 0;
+    const uint32_t idx = FUSED ? uint32_t(raw) & 0x7FFFFFFFu : uint32_t(raw);
+    const bool inb = FUSED ? int(idx) <= cache_lim + (sgn & (fresh_lim - cache_lim)) : idx < uint32_t(a.num_blocks);
+    auto where = [&](uint32_t i) __attribute__((always_inline)) -> const uint8_t* {
+      if constexpr (FUSED) return c_src + (int64_t(sgn) & c_delta) + uint64_t(i) * row_bytes;
+      else return c_src + uint64_t(i) * blk_bytes;
+    };
+    auto copies = [&](const uint8_t* src) __attribute__((always_inline)) {
+      cp_src = src;
+      cp_dst = dst;
+      cp_stride = 1024;
+      if constexpr (FUSED) cp_off = neg ? off_n : off_c;
+    };
+    // fast path: a whole block, the next word inside the prompt's blocks, the
+    // cursor stays in its entry (c_fast > 0 implies !cdone)
+    if (__builtin_expect(c_fast > 0 && inb, 1)) {
+      const uint8_t* src = where(idx);
+      if constexpr (FUSED) dring = lane == ring ? dword : dring;
+      --c_fast;
+      --c_left;
+      c_lb += kKv / kBs;
+      c_ptr += (kKv / kBs) * TW;
+      bw_ptr = c_ptr;
+      copies(src);
+      return;
+    }
+    cp_src = cache;
+    cp_dst = own_area;
+    cp_stride = 0;
+    cp_off = off_c;
+    if (cdone) {
+      if constexpr (FUSED) dring = lane == ring ? -1 : dring;
+      return;
+    }
+    const int lb = c_lb, L = c_L;
+    const int key0 = lb * kBs;
+    // a block inside the prompt whose rows up to the prompt's end lie inside
+    // the source tensor (a partial block of k_new / v_new rows is not read
+    // past the prompt: the last request's end is the tensor's end)
+    const bool valid = lb <= c_last && (neg ? int64_t(idx) + (L - 1 - key0) < a.total_rows : inb);
+    const bool whole = valid && lb < c_whole;
+    const uint8_t* src = valid ? where(idx) : c_src;
+    if constexpr (FUSED) dring = lane == ring ? (lb <= c_last ? dword : -1) : dring;
+    c_lb += kKv / kBs;
+    c_fast = max(0, c_fast - 1);
+    if (--c_left == 0) cursor_take();
+    cursor_load();
+    if (whole) {   // wave-uniform: the whole block is valid
+      copies(src);
+      return;
+    }
+    cp_keys = valid ? L - key0 : 0;
+    cp_psrc = src;
+    cp_slot = dst;
+    cp_poff = (neg && valid) ? uint32_t(min(ckey, L - 1 - key0)) * row_bytes + uint32_t((lane >> 4) << 4) : off_c;
+  };
+  // A block that is not whole: through registers, zeros past its keys (a missing
+  // block loads block 0 and discards it).
+  auto stage_partial = [&]() __attribute__((always_inline)) {
+    if (__builtin_expect(cp_keys >= 0, 0)) {
+#pragma unroll
+      for (int i = 0; i < LPW; ++i) {
+        u32x4 v = load16_now(cp_psrc + cp_poff + 64 * i);
+        v = ckey < cp_keys ? v : u32x4{0, 0, 0, 0};
+        *reinterpret_cast<u32x4*>(lds + (cp_slot - lds0) + i * 1024 + lane * 16) = v;
+      }
+      cp_keys = -1;
+    }
+  };
+  auto issue = [&](int pp) __attribute__((always_inline)) {
+    prepare(pp);
+    load_bword();
+    stage_partial();
+#pragma unroll
+    for (int k = 0; k < LPW; ++k) copy16_to_lds(cp_src, cp_off, cp_dst + k * cp_stride, k);
+  };
+  // Workgroup barrier between intervals; the empty asm statements keep the
+  // compiler from moving memory accesses across it, the scheduling barriers
+  // from moving instructions of one interval into another.
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const bool group1 = wave >= 4;
+
+  // ---- per-lane LDS read offsets (ring position 0; a position adds its stride)
+  // K operand: key 32 h + pi(l32) (block 2 h + l32 / 16, row pi(l32) % 16),
+  // chunk 2 s + half; in the chunk-major block layout that is the lane's base
+  // plus h 32 RB + s 512.
+  const int k_row = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
+  int k_off = (l32 >> 4) * (kBs * RB) + half * 256 + (k_row & 15) * 16;
+  // V operand (transposing reads, two per operand): in each 16-lane group a
+  // lane names 4 values of d of one key, and lane 4 q + s receives value s of
+  // the 4 keys named by lanes q, q + 4, q + 8, q + 12. Lane j of group gq names
+  // key 8 half + 4 rd + j / 4 of the block (rd: first or second read) and
+  // d = 32 t + 16 (gq % 2) + 4 (j % 4), so lane l32 receives row d = 32 t + l32,
+  // keys 8 half + 4 rd .. + 3: with both reads the operand of keys
+  // 8 half .. + 7. In the swizzled chunk-major layout that is the lane's base
+  // (chunk c % 4 = 2 (gq % 2) + (j % 4) / 2) plus t 1024 + kk BLK.
+  const int vj = lane & 15, vpart = 2 * ((lane >> 4) & 1) + ((vj & 3) >> 1);
+  int v_off0 = KREG + vpart * 256 + (((8 * half + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
+  int v_off1 = KREG + vpart * 256 + (((8 * half + 4 + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
+  // Hide the bases' known bits from the compiler: otherwise it rewrites
+  // base + constant as base | constant, which it cannot fold into the LDS
+  // instructions' offset field, and keeps one register per read instead.
+  asm volatile("" : "+v"(k_off));
+  asm volatile("" : "+v"(v_off0));
+  asm volatile("" : "+v"(v_off1));
+  auto rd16 = [&](int addr) __attribute__((always_inline)) -> bf16x8 {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + addr));
+  };
+  auto rdtr = [&](int addr) __attribute__((always_inline)) -> u32x2 {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    auto* lp = (__attribute__((address_space(3))) uint8_t*)lds + addr;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)lp));
+  };
+
+  // This lane's query column inside a tile: head hh of the group, position pos.
+  const int m = wave * 32 + l32;
+  const int hh = m / a.per_tile;
+  const int pos = m - hh * a.per_tile;
+
+  // Queries, scaled, of the step whose scores come next. Those of the entry to
+  // come are loaded in the softmax interval of the current entry's last step
+  // (their lines were brought into L2 in its first).
+  bf16x8 qf[KS];
+  // Plan words of an entry, word l % 16 in lane l: d1 of the entry after the
+  // current one, d2 of the one after that.
+  int32_t d1 = 0, d2 = 0;
+  auto word = [&](int32_t d, int i) __attribute__((always_inline)) -> int { return __builtin_amdgcn_readlane(d, i); };
+  // whether d holds the words the planner wrote for this batch at index e
+  auto entry_ok = [&](int32_t d, int e) __attribute__((always_inline)) -> bool {
+    return e < a.num_entries && word(d, cw::kEntR) >= 0 &&
+           uint32_t(word(d, cw::kEntCheck)) == cw::entry_tag(a.fp_lo, a.fp_hi, uint32_t(e));
+  };
+  auto steps_of = [&](int32_t d) __attribute__((always_inline)) -> int {
+    return word(d, cw::kEntKend) - word(d, cw::kEntKbeg);
+  };
+  // whether this lane's query column exists in the entry of d
+  auto has_row = [&](int32_t d) __attribute__((always_inline)) -> bool {
+    return hh < a.group && pos < word(d, cw::kEntNvalid);
+  };
+  // This lane's Q row in the entry of d; row 0 of Q for a lane without a row or
+  // without an entry (the load stays inside Q and its value is not used).
+  auto q_row = [&](int32_t d, bool exists) __attribute__((always_inline)) -> const u32x4* {
+    int64_t off = 0;
+    if (exists) {
+      const int64_t row = int64_t(word(d, cw::kEntQrow)) + pos;
+      const int hd = word(d, cw::kEntG) * a.group + hh;
+      off = has_row(d) ? (row * a.hq + hd) * D : 0;
+    }
+    return reinterpret_cast<const u32x4*>(a.q + off);
+  };
+  // Loads and scales the queries of the entry of d (zeros for a lane without a
+  // row), in one asm block with its wait: the loaded registers live only here.
+  auto form_q = [&](int32_t d, bool exists) __attribute__((always_inline)) {
+    const u32x4* qp = q_row(d, exists) + half;
+    const bool ok = has_row(d);
+    u32x4 raw[KS];
+    if constexpr (KS == 8)
+      asm volatile("global_load_dwordx4 %0, %8, off\n\tglobal_load_dwordx4 %1, %8, off offset:32\n\t"
+                   "global_load_dwordx4 %2, %8, off offset:64\n\tglobal_load_dwordx4 %3, %8, off offset:96\n\t"
+                   "global_load_dwordx4 %4, %8, off offset:128\n\tglobal_load_dwordx4 %5, %8, off offset:160\n\t"
+                   "global_load_dwordx4 %6, %8, off offset:192\n\tglobal_load_dwordx4 %7, %8, off offset:224\n\t"
+                   "s_waitcnt vmcnt(0)"
+                   : "=&v"(raw[0]), "=&v"(raw[1]), "=&v"(raw[2]), "=&v"(raw[3]), "=&v"(raw[KS - 4]),
+                     "=&v"(raw[KS - 3]), "=&v"(raw[KS - 2]), "=&v"(raw[KS - 1])
+                   : "v"(qp) : "memory");
+    else
+      asm volatile("global_load_dwordx4 %0, %4, off\n\tglobal_load_dwordx4 %1, %4, off offset:32\n\t"
+                   "global_load_dwordx4 %2, %4, off offset:64\n\tglobal_load_dwordx4 %3, %4, off offset:96\n\t"
+                   "s_waitcnt vmcnt(0)"
+                   : "=&v"(raw[0]), "=&v"(raw[1]), "=&v"(raw[2]), "=&v"(raw[3]) : "v"(qp) : "memory");
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      qf[s] = ok ? scale_bf16x8(raw[s], a.c_log2) : __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
+  };
+  // ---- the queue's first entry
+  int e_cur = blockIdx.x;
+  int32_t d0 = load_word_untracked(entry_word_addr(e_cur));
+  // the wait that completes the words (and the table word loaded before),
+  // tied to the register that receives them
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(d0) :: "memory");
+  if (!entry_ok(d0, e_cur)) return;   // (the same for every wave)
+  d1 = load_word_untracked(entry_word_addr(e_cur + grid));
+  // ---- first steps of the queue: two, and a third by group 1
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (i < 2 || group1) issue(i);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : "+v"(d1) :: "memory");
+  barrier();
+
+  // Output rows of the staged read-back : the lanes reading
+  // staged row rr hold column m' = 32 wave + rr of the tile, i.e. head m' / T
+  // and position m' % T (T = a.per_tile; the quotient by a multiply, exact for
+  // m' < 256).
+  const uint32_t tdiv = (65536u + uint32_t(a.per_tile) - 1) / uint32_t(a.per_tile);
+
+  f32x16 sc[2];      // scores of the step whose softmax comes next
+  f32x16 oacc[DT];
+  f32x16 mneg;       // -base in every element: the start of each score accumulator
+  uint32_t w[16];    // packed probabilities
+  float l_run = 0.f; // this lane's partial row sum (its 32 keys per step)
+  const bf16x2 ones{(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+  for (int t = 0; t < DT; ++t) oacc[t] = f32x16{};
+#pragma unroll
+  for (int i = 0; i < 16; ++i) mneg[i] = 0.f;
+
+  // K operand of QK MFMA i (k-step i / 2 over D, 32-key half i % 2) of the
+  // stage at kb; V operand of PV MFMA i (16-key slice i / DT, output tile
+  // i % DT) of the stage at vb.
+  auto rdk = [&](int kb, int i) __attribute__((always_inline)) -> bf16x8 {
+    return rd16(kb + (i & 1) * 32 * RB + (i >> 1) * 512);
+  };
+  auto rdv = [&](int vb, int i) __attribute__((always_inline)) -> bf16x8 {
+    const int o = vb + (i / DT) * BLK + (i % DT) * 1024;
+    const u32x2 lo = rdtr(v_off0 + o), hi = rdtr(v_off1 + o);
+    return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+  };
+  auto kbase = [&](int pp) { return k_off + (pp & (kStages - 1)) * KTILE; };
+  auto vbase = [&](int pp) { return (pp & (kStages - 1)) * VTILE; };
+  // Operands in flight ahead of their MFMA.
+  constexpr int RA = DT == 4 ? 6 : 4;
+  constexpr int NPV = 4 * DT, NQK = 2 * KS, N = NPV + NQK;
+  bf16x8 op[RA];
+  auto read_op = [&](int pp, int i) __attribute__((always_inline)) {
+    op[i % RA] = i < NPV ? rdv(vbase(pp), i) : rdk(kbase(pp + 1), i - NPV);
+  };
+  // Product interval of the step at ring position pp: O^T += V^T P^T of the
+  // step, then the scores S^T = K Q^T of the step after it (the next entry's
+  // first step after an entry's last; unused after the queue's last). The first
+  // RA operands were read before the barrier (V of this step landed an interval
+  // earlier). MFMA and operand read alternate, fenced so that the compiler
+  // keeps the read-ahead. Any vector work put between the products delays them
+  // (row sums and maxima there: 1,405 cycles instead of 1,045); the row sums
+  // follow them (they use the rounded probabilities the PV product uses).
+  auto products = [&](int pp) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (i < NPV) {
+        const int kk = i / DT;
+        const bf16x8 pk = __builtin_bit_cast(bf16x8, u32x4{w[4 * kk], w[4 * kk + 1], w[4 * kk + 2], w[4 * kk + 3]});
+        oacc[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i % RA], pk, oacc[i % DT], 0, 0, 0);
+      } else {
+        const int q = i - NPV;
+        sc[q & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[i % RA], qf[q >> 1], q < 2 ? mneg : sc[q & 1], 0, 0, 0);
+      }
+      if (i + RA < N) read_op(pp, i + RA);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    float ls[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      ls[i & 1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[i]), ones, ls[i & 1], false);
+    l_run += ls[0] + ls[1];
+    asm volatile("" : "+v"(l_run));
+  };
+
+  // ---- the first step's scores, one group after the other
+  form_q(d0, true);
+  if (group1) barrier();   // group 1 runs one interval behind
+  {
+    bf16x8 kf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kf[i] = rdk(kbase(0), i);
+#pragma unroll
+    for (int i = 0; i < NQK; ++i) {
+      sc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i & 3], qf[i >> 1], i < 2 ? mneg : sc[i & 1], 0, 0, 0);
+      if (i + 4 < NQK) kf[i & 3] = rdk(kbase(0), i + 4);
+    }
+  }
+  barrier();
+
+  int p = 0;   // ring position of the current step
+  bool more = true;
+  while (more) {
+    // ---- the current entry (its words are in d0, the next entry's in d1)
+    const int g = word(d0, cw::kEntG), row0 = word(d0, cw::kEntRow0);
+    const int nvalid = word(d0, cw::kEntNvalid), P = word(d0, cw::kEntP);
+    const int qrow0 = word(d0, cw::kEntQrow);
+    const int kbeg = word(d0, cw::kEntKbeg);
+    const int nsteps = steps_of(d0);
+    // steps [0, n_full) are visible to every row of the entry (no mask)
+    const int n_full = word(d0, cw::kEntNfull);
+    const bool row_ok = has_row(d0);
+    const int qpos = P + row0 + pos;  // keys 0 .. qpos are visible
+    const int e_next = e_cur + grid;
+
+    // FUSED: the keys of this entry's query rows are new keys of this call.
+    // Where this wave's block of step j (ring position p) holds some of them (an
+    // entry's last steps), the wave writes those rows from the stage into the
+    // block's place in its cache (the destination recorded when the block was
+    // copied; -1 where the call writes nothing). Lane l's 16 bytes at
+    // 1024 it + 16 l of its slot are the bytes it copied, chunk 4 it + l / 16 of
+    // key ckey, so they go to the same offset of the destination block.
+    // Returns whether LPW stores were issued (a block owned whole); a block
+    // owned in part (a request's last rows, or tiles of fewer than 16
+    // positions) is stored by the lanes of its rows.
+    const int own_j0 = (P + row0) / kKv - kbeg;   // steps before it write nothing
+    auto write_own = [&](int j) __attribute__((always_inline)) -> bool {
+      const int key0 = ((kbeg + j) * (kKv / kBs) + bs) * kBs;
+      const int lo = max(key0, P + row0), hi = min(key0 + kBs, P + row0 + nvalid);
+      const int dstb = __builtin_amdgcn_readlane(dring, p & (kStages - 1));
+      if (uint32_t(dstb) >= uint32_t(a.num_blocks) || lo >= hi) return false;
+      const uint32_t sb = slot0 - lds0 + uint32_t(p & (kStages - 1)) * stage_stride;
+      u32x4 t[LPW];
+#pragma unroll
+      for (int it = 0; it < LPW; ++it) t[it] = *reinterpret_cast<const u32x4*>(lds + sb + it * 1024 + lane * 16);
+      uint8_t* dp = reinterpret_cast<uint8_t*>(is_v ? a.vw : a.kw) + uint64_t(uint32_t(dstb)) * blk_bytes +
+                    uint32_t(g) * (kBs * RB) + off_c;
+      if (lo == key0 && hi == key0 + kBs) {
+#pragma unroll
+        for (int it = 0; it < LPW; ++it) {
+          // (a store of more than 8 bytes reads its data registers after issue:
+          // wait states before an instruction may write them)
+          asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" :: "v"(dp + 64 * it), "v"(t[it]) : "memory");
+        }
+        return true;
+      }
+      const bool mine = key0 + ckey >= lo && key0 + ckey < hi;
+#pragma unroll
+      for (int it = 0; it < LPW; ++it)
+        if (mine) *reinterpret_cast<u32x4*>(dp + 64 * it) = t[it];
+      return false;
+    };
+
+    for (int j = 0; j < nsteps; ++j) {
+      // ---- softmax interval of step j. In step 0 the next entry's queries are
+      // brought into L2 and the words after it loaded, then the copies of the step two (group 0) or three
+      // (group 1) ahead.
+      if (__builtin_expect(j == 0, 0)) {
+        touch_line(reinterpret_cast<const uint8_t*>(q_row(d1, entry_ok(d1, e_next))) + half * RB / 2, own_area);
+        d2 = load_word_untracked(entry_word_addr(e_next + grid));
+      }
+      issue(p + (group1 ? 3 : 2));
+
+      // Causal mask of the step starting at key k0: element e of accumulator h
+      // holds key k0 + 32 h + (e / 8) 16 + half 8 + e % 8; the lane term moves to
+      // the limit so that the per-element terms stay immediates.
+      // (each element is pinned after its select: otherwise the compiler keeps
+      // all 32 compare results live as lane masks in scalar registers)
+      if (__builtin_expect(j >= n_full, 0)) {
+        const int lim = qpos - (kbeg + j) * kKv - half * 8;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e2 = 0; e2 < 16; ++e2) {
+            if (h * 32 + (e2 >> 3) * 16 + (e2 & 7) > lim) sc[h][e2] = -INFINITY;
+            asm volatile("" : "+v"(sc[h][e2]));
+          }
+      }
+      // Maximum of the row over the step's 64 keys (this lane's 32 and lane ^ 32's).
+      float mx;
+      {
+        float x = fmaxf(fmaxf(sc[0][0], sc[0][1]), sc[0][2]);
+        float y = fmaxf(fmaxf(sc[1][0], sc[1][1]), sc[1][2]);
+#pragma unroll
+        for (int e2 = 3; e2 < 15; e2 += 2) {
+          x = fmaxf(fmaxf(x, sc[0][e2]), sc[0][e2 + 1]);
+          y = fmaxf(fmaxf(y, sc[1][e2]), sc[1][e2 + 1]);
+        }
+        x = fmaxf(fmaxf(x, sc[0][15]), sc[1][15]);
+        mx = max_pair32(fmaxf(x, y));
+      }
+      if (__builtin_expect(j == 0, 0)) {
+        // The first step's exact row maximum is the base. Finite when the run's
+        // first step has a visible key for this row (always so for the first
+        // run: key 0 is visible to every row). A row that sees no key of the
+        // run's first step sees none of its later steps either (they hold
+        // higher keys), so any base serves it.
+        const float m0 = mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) sc[h] -= m0;
+#pragma unroll
+        for (int e2 = 0; e2 < 16; ++e2) mneg[e2] = -m0;
+      } else {
+        // Moves the base up by the step maximum when it exceeds it by kLazy.
+        const bool grow = mx > kLazy;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(grow) != 0, 0)) {
+          const float delta = grow ? mx : 0.f;
+          const float alpha = __builtin_amdgcn_exp2f(-delta);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) sc[h] -= delta;
+          mneg -= delta;
+          l_run *= alpha;
+#pragma unroll
+          for (int t = 0; t < DT; ++t) oacc[t] *= alpha;
+        }
+      }
+      // Probabilities, packed to bf16 (w[4 kk + jj]: keys 2 jj, 2 jj + 1 of the
+      // lane half's 8 in 16-key slice kk).
+      {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int kk = i >> 2, jj = i & 3, h = kk >> 1, e2 = (kk & 1) * 8 + 2 * jj;
+          w[i] = pack_bf16x2(__builtin_amdgcn_exp2f(sc[h][e2]), __builtin_amdgcn_exp2f(sc[h][e2 + 1]));
+        }
+      }
+      if (__builtin_expect(j == nsteps - 1, 0)) {
+        // the next scores are the next entry's: its queries, and base 0
+        form_q(d1, entry_ok(d1, e_next));
+#pragma unroll
+        for (int e2 = 0; e2 < 16; ++e2) mneg[e2] = 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < RA; ++i) read_op(p, i);
+      bool late = false;
+      if constexpr (FUSED) {
+        if (j >= own_j0) late = write_own(j);
+      }
+      // Group 0's products read the K of the next step, whose copies must have
+      // landed in every wave: group 0's were made in its last softmax interval
+      // (before an entry's first step they are waited for at the last entry's
+      // end), group 1's are waited for below.
+      if (!group1 && j > 0) {
+        if (__builtin_expect(late, 0)) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LPW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LPW) : "memory");
+      }
+      barrier();
+
+      // ---- product interval
+      products(p);
+      // Group 1's copies of the last softmax interval but one, which group 0
+      // reads in its next product interval, have landed.
+      if (group1) {
+        if (__builtin_expect(late, 0)) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LPW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LPW) : "memory");
+      }
+      barrier();
+      ++p;
+
+      if (__builtin_expect(j < nsteps - 1, 1)) continue;
+      // ---- the entry's end (part of the next softmax interval). Copies first:
+      // a later wait for them would wait for the output's stores too.
+      // (and copies to this wave's own area must not meet the output staged there)
+      if (late) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LPW) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const float l_tot = sum_pair32(l_run);
+      {
+        // The output goes through this wave's staging area: a lane holds 4
+        // consecutive d of its row per (t, gq), so direct stores would write 32
+        // rows in 8-byte pieces per instruction. Each round stages a range of d
+        // (HD values) of all 32 rows and reads it back as rows of 16-byte
+        // chunks, so that each store covers whole 128-byte lines of HD values
+        // (16-byte chunk c of staged row r at position c ^ (r % CPR):
+        // conflict-free writes and reads). Lanes read what other lanes wrote:
+        // the hardware keeps a wave's LDS accesses in order, and empty asm
+        // statements with a memory clobber keep the compiler from reusing, for
+        // a lane, values it loaded before another lane's writes (as it may, for
+        // memory it sees no other thread write).
+        constexpr int HD = G::STAGING / (32 * 2);   // d values per round (64)
+        constexpr int CPR = HD / 8;                // 16-byte chunks per staged row
+        constexpr int TPR = HD / 32;               // output tiles per round
+        constexpr int RPI = 64 / CPR;              // staged rows per read instruction
+        static_assert(D % HD == 0 && CPR == 8, "staging rounds");
+        const float inv = row_ok ? __builtin_amdgcn_rcpf(l_tot) : 0.f;
+        uint8_t* stg = lds + G::RING + wave * G::STAGING;
+        // Opaque copies of the values the addresses below derive from: without
+        // them the compiler computes those (entry- or lane-invariant) addresses
+        // before the steps and keeps them live across the step loop.
+        int ln = lane, q0 = qrow0, nv = nvalid, hg = g * a.group;
+        asm volatile("" : "+v"(ln), "+s"(q0), "+s"(nv), "+s"(hg));
+        const int l32e = ln & 31, halfe = ln >> 5;
+#pragma unroll
+        for (int rd = 0; rd < D / HD; ++rd) {
+#pragma unroll
+          for (int tt = 0; tt < TPR; ++tt)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+              const int t = rd * TPR + tt, c = tt * 4 + gq;   // d = 32 t + 8 gq + 4 half ..
+              const u32x2 w2{pack_bf16x2(oacc[t][gq * 4 + 0] * inv, oacc[t][gq * 4 + 1] * inv),
+                             pack_bf16x2(oacc[t][gq * 4 + 2] * inv, oacc[t][gq * 4 + 3] * inv)};
+              *reinterpret_cast<u32x2*>(stg + l32e * (HD * 2) + ((c ^ (l32e % CPR)) << 4) + halfe * 8) = w2;
+            }
+          asm volatile("" ::: "memory");
+          // all of the round's reads first, then the stores of the rows that exist
+          u32x4 v[32 / RPI];
+#pragma unroll
+          for (int q = 0; q < 32 / RPI; ++q) {
+            const int r = q * RPI + ln / CPR, c = ln % CPR;
+            v[q] = *reinterpret_cast<const u32x4*>(stg + r * (HD * 2) + ((c ^ (r % CPR)) << 4));
+          }
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int q = 0; q < 32 / RPI; ++q) {
+            const int r = q * RPI + ln / CPR, c = ln % CPR;
+            // the staged row's column of the tile, its head and position
+            const uint32_t mr = uint32_t(wave * 32 + r);
+            const int hr = int((mr * tdiv) >> 16);
+            const int pr = int(mr) - hr * a.per_tile;
+            if (hr < a.group && pr < nv)
+              *reinterpret_cast<u32x4*>(a.out + ((int64_t(q0) + pr) * a.hq + hg + hr) * D + rd * HD + c * 8) = v[q];
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < DT; ++t) oacc[t] = f32x16{};
+      l_run = 0.f;
+    }
+    // ---- on to the next entry (d2 landed before the queries were formed)
+    more = entry_ok(d1, e_next);
+    asm volatile("" : "+v"(d2));
+    d0 = d1;
+    d1 = d2;
+    e_cur = e_next;
+  }
+  if (!group1) barrier();
+  // Every copy the cursor issued was consumed: the cursor runs out with the
+  // last entry, and every issued step is computed before the loop ends.
+}
+
+// ---------------------------------------------------------------------------
 // Log-sum-exp merge of attention results over disjoint key sets: for each row,
 // out = sum_p 2^(lse_p - M) o_p / sum_p 2^(lse_p - M), M = max_p lse_p, where o_p
 // is part p's normalised output and lse_p its base-2 log-sum-exp (-inf for a
@@ -1371,6 +2074,7 @@ namespace {
 struct AttnLaunch {
   AttnArgs args;
   int32_t grid = 0, splits = 1;
+  int64_t steps = 0, tiles = 0;   // 64-key steps and tiles of an unsplit plan
   int64_t rows = 0;
 };
 cw_status check_attn(const char* what, const void* q, const void* k_cache, const void* v_cache,
@@ -1424,11 +2128,35 @@ cw_status check_attn(const char* what, const void* q, const void* k_cache, const
   a.per_tile = cw::tile_positions(group);
   a.num_blocks = num_blocks;
   a.c_log2 = softmax_scale * 1.4426950408889634f;
+  // (the header's work counts the steps of every entry and one more)
+  L->tiles = cw::count_tiles(cu_suffix_host, batch, num_kv_heads, a.per_tile);
+  L->steps = plan_host[cw::kHdrWork] - L->tiles;
   return CW_OK;
+}
+
+// Whether an unsplit call takes the alternating kernel; both give the same bits.
+// It gains on every step and pays at an entry's end, which takes the two groups
+// one after the other. Both in turn on one card, us, interleaved / alternating,
+// by mean steps of an entry (entries): 64 (120) 112 / 101, 43 (680) 226 / 218, 26
+// (192) 53.5 / 51.4, 19 (328) 63.3 / 63.0; 14 (2,080: 115 steps a queue) 244 /
+// 241, 14 (512: 29 a queue) 67.4 / 66.4, 16 (296: 19 a queue) 54.5 / 55.2; 8
+// (528) 54 / 56, 5 (616) 46.7 / 49.7. Hence 17 steps an entry, or 14 where the
+// queues are long as well. At head_dim 64 the products are half as long and the
+// softmax is not: 13 (276) 30.1 / 33.5.
+bool long_entries(int head_dim, const AttnLaunch& L) {
+  if (head_dim != 128) return false;
+  return L.steps >= 17 * L.tiles || (L.steps >= 14 * L.tiles && L.steps >= 28 * int64_t(L.grid));
 }
 
 template <bool SPLIT, bool FUSED = false>
 void launch_attn(int head_dim, const AttnLaunch& L, hipStream_t s) {
+  if constexpr (!SPLIT) {
+    if (long_entries(head_dim, L)) {
+      hipLaunchKernelGGL((suffix_prefill_stream_kernel<128, FUSED>), dim3(unsigned(L.grid)), dim3(kAttnThreads), 0, s,
+                         L.args);
+      return;
+    }
+  }
   if (head_dim == 128)
     hipLaunchKernelGGL((suffix_prefill_attn_kernel<128, SPLIT, FUSED>), dim3(unsigned(L.grid)), dim3(kAttnThreads),
                        0, s, L.args);

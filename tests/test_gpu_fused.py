@@ -165,3 +165,37 @@ def test_fused_runner_matches_sequential_calls_bitwise():
     assert torch.equal(v0.view(torch.int16), db.v_cache.view(torch.int16))
     rn.release(pool)
     GP._cleanup()
+
+
+def _steps(meta):
+    return int(meta.plan_host[cw.HDR_WORK]) - meta.num_tiles
+
+
+LONG_S = [1, 15, 16, 17, 300, 0, 33, 64]
+LONG_P = [1008, 1024, 2048, 1600, 1024, 32, 1504, 912]
+
+
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (8, 2), (32, 8), (28, 4), (64, 1), (128, 1), (96, 3)])
+def test_long_entries_match_oracle_and_short_batch_bits(hq, hkv):
+    """Entries of many steps take the alternating kernel: single-row, partial
+    block, one- and several-tile suffixes over long prefixes against the oracle,
+    the fused call against the separate ones bit for bit, and the same requests
+    among many short ones (entries of few steps: the other kernel) bit for bit."""
+    w = GP._ragged(hq, hkv, 128, LONG_S, LONG_P, seed=hq + 11)
+    GP._say(f"long entries {w.name}")
+    seq, fus = B.materialize(w), B.materialize(w, keep_host=[])
+    out_s = GP._run(seq)
+    GP._compare_full(seq, out_s)
+    assert torch.equal(_fused(fus).view(torch.int16), out_s.view(torch.int16))
+    assert torch.equal(fus.k_cache.view(torch.int16), seq.k_cache.view(torch.int16))
+    assert torch.equal(fus.v_cache.view(torch.int16), seq.v_cache.view(torch.int16))
+    steps, tiles = _steps(seq.meta), seq.meta.num_tiles
+    assert steps >= 17 * tiles
+    n = 400   # suffix of an extra request without a prefix: at most seven steps a tile
+    extra = -(-2 * tiles * 256 // (n * hq)) + 2
+    w2 = GP._ragged(hq, hkv, 128, LONG_S + [n] * extra, LONG_P + [0] * extra, seed=hq + 11)
+    both = B.materialize(w2, keep_host=[])
+    assert _steps(both.meta) < 14 * both.meta.num_tiles
+    out_b = GP._run(both)
+    assert torch.equal(out_b[:out_s.shape[0]].view(torch.int16), out_s.view(torch.int16))
+    GP._cleanup()
