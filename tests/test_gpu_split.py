@@ -69,6 +69,23 @@ def test_lse_merge_matches_oracle(parts, rows, d):
     _check(got, expect, f"lse_merge parts={parts} rows={rows} d={d}")
 
 
+@pytest.mark.parametrize("parts", [1, 2, 3, 4, 5, 8, 9])
+def test_lse_merge_ignores_values_of_empty_parts(parts):
+    """Every part count of the merge kernels, and one more than their chunks:
+    a part whose log-sum-exp is -inf counts for nothing, NaN values included."""
+    g = torch.Generator().manual_seed(parts)
+    rows, d = 53, 24
+    o = torch.randn((parts, rows, d), generator=g, dtype=torch.float32)
+    lse = (torch.rand((parts, rows), generator=g) * 20 - 10).float()
+    drop = torch.rand((parts, rows), generator=g) < 0.4
+    lse[drop] = -float("inf")
+    expect = OA.lse_merge(torch.where(drop[..., None], 0.0, o).numpy(), lse.numpy())
+    o[drop] = float("nan")
+    got = cw.lse_merge(o.cuda(), lse.cuda())
+    torch.cuda.synchronize()
+    _check(got.float().cpu().numpy(), expect, f"lse_merge with NaN in empty parts, parts={parts}")
+
+
 @pytest.mark.parametrize("splits", [1, 2, 4, 7])
 def test_split_question_only(splits):
     w = W.question_only()
