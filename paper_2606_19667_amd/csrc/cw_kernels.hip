@@ -1213,20 +1213,48 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
 
     const float l_tot = sum_pair32(l_run);
     if constexpr (SPLIT) {
-      if (!row_ok) continue;
-      const int64_t prow = int64_t(split) * a.part_rows + qrow * a.hq + head;
-      float* po = a.part_o + prow * D;
+      // Partial output in fp32, through this wave's staging area (as the
+      // unsplit output below): a lane holds 4 consecutive d of its row per
+      // (t, gq), so direct stores would write 32 rows in 32-byte pieces per
+      // instruction. Each round stages 32 values of d of all 32 rows (16-byte
+      // chunk c of row r at position c ^ (r % 8)) and stores whole 128-byte
+      // lines: 576 rows, 32 query heads, 3 runs 28.3 us with direct stores, 26.8 now.
       const bool any = l_tot > 0.f;
       const float inv = any ? 1.f / l_tot : 0.f;
+      uint8_t* stg = lds + G::RING + wave * G::STAGING;
+      static_assert(G::STAGING == 32 * 32 * 4, "one 32 x 32 fp32 tile a round");
+      int ln = lane, q0 = qrow0, nv = nvalid, hg = g * a.group;
+      asm volatile("" : "+v"(ln), "+s"(q0), "+s"(nv), "+s"(hg));
+      const int l32e = ln & 31, halfe = ln >> 5;
+      float* const part = a.part_o + int64_t(split) * a.part_rows * D;
 #pragma unroll
-      for (int t = 0; t < DT; ++t)
+      for (int t = 0; t < DT; ++t) {
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq)
-          *reinterpret_cast<f32x4*>(po + t * 32 + gq * 8 + half * 4) =
+        for (int gq = 0; gq < 4; ++gq)   // d = 32 t + 8 gq + 4 half ..
+          *reinterpret_cast<f32x4*>(stg + l32e * 128 + (((2 * gq + halfe) ^ (l32e & 7)) << 4)) =
               f32x4{oacc[t][gq * 4 + 0] * inv, oacc[t][gq * 4 + 1] * inv, oacc[t][gq * 4 + 2] * inv,
                     oacc[t][gq * 4 + 3] * inv};
+        asm volatile("" ::: "memory");
+        f32x4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = q * 8 + (ln >> 3);
+          v[q] = *reinterpret_cast<const f32x4*>(stg + r * 128 + (((ln & 7) ^ (r & 7)) << 4));
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          // the staged row's column of the tile, its head and position
+          const uint32_t mr = uint32_t(wave * 32 + q * 8 + (ln >> 3));
+          const int hr = int((mr * tdiv) >> 16);
+          const int pr = int(mr) - hr * a.per_tile;
+          if (hr < a.group && pr < nv)
+            *reinterpret_cast<f32x4*>(part + ((int64_t(q0) + pr) * a.hq + hg + hr) * D + t * 32 + (ln & 7) * 4) = v[q];
+        }
+      }
       // base-2 log-sum-exp of the scaled scores: the base plus log2 of the sum
-      if (half == 0) a.part_lse[prow] = any ? -mneg[0] + __log2f(l_tot) : -INFINITY;
+      if (row_ok && half == 0)
+        a.part_lse[int64_t(split) * a.part_rows + qrow * a.hq + head] = any ? -mneg[0] + __log2f(l_tot) : -INFINITY;
     } else {
       // The output goes through this wave's staging area: a lane holds 4
       // consecutive d of its row per (t, gq), so direct stores would write 32
