@@ -146,7 +146,16 @@ def _i32_array(x, name: str) -> np.ndarray:
 
 
 def _ptr(a: np.ndarray, ctype):
-    return a.ctypes.data_as(ctypes.POINTER(ctype)) if a.size else None
+    """An argument for a POINTER(ctype) parameter: the array's first element (a
+    ctypes object on the array's own memory, which it keeps alive). A device
+    call passes up to four; numpy's data_as takes ten times as long, and is
+    left for arrays that are not writable or not contiguous."""
+    if not a.size:
+        return None
+    try:
+        return ctype.from_buffer(a)
+    except (TypeError, ValueError, BufferError):
+        return a.ctypes.data_as(ctypes.POINTER(ctype))
 
 
 # ---------------------------------------------------------------- host calls
@@ -369,7 +378,7 @@ def append_table(plan: np.ndarray) -> np.ndarray:
 def _dev(t: torch.Tensor, dtype, name: str) -> int:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be in GPU memory")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
@@ -379,8 +388,8 @@ def _dev(t: torch.Tensor, dtype, name: str) -> int:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:   # the handle of torch.cuda.current_stream(), without the object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream)
 
 
@@ -487,8 +496,8 @@ class BatchMeta:
 
 def _cache_shapes_ok(k_cache: torch.Tensor, v_cache: torch.Tensor, hkv: int, D: int) -> bool:
     """Both caches are [num_blocks, Hkv, 16, D] (block rows are tokens)."""
-    return (k_cache.dim() == 4 and v_cache.dim() == 4 and tuple(k_cache.shape[1:]) == (hkv, BLOCK_SIZE, D)
-            and tuple(v_cache.shape) == tuple(k_cache.shape))
+    return (k_cache.dim() == 4 and v_cache.dim() == 4 and k_cache.shape[1:] == (hkv, BLOCK_SIZE, D)
+            and v_cache.shape == k_cache.shape)
 
 
 def kv_append(meta: BatchMeta, k_new: torch.Tensor, v_new: torch.Tensor, k_cache: torch.Tensor,
@@ -498,7 +507,7 @@ def kv_append(meta: BatchMeta, k_new: torch.Tensor, v_new: torch.Tensor, k_cache
         meta.check_device_copies()
     hkv, D = meta.num_kv_heads, meta.head_dim
     for name, t in (("k_new", k_new), ("v_new", v_new)):
-        if tuple(t.shape) != (meta.total_rows, hkv, D):
+        if t.shape != (meta.total_rows, hkv, D):
             raise ValueError(f"{name} must be [{meta.total_rows}, {hkv}, {D}], got {tuple(t.shape)}")
     if not _cache_shapes_ok(k_cache, v_cache, hkv, D):
         raise ValueError("k_cache and v_cache must both be [num_blocks, Hkv, 16, D]")
@@ -524,17 +533,17 @@ def qkv_rope_append(meta: BatchMeta, x: torch.Tensor, w: torch.Tensor, rope: tor
         raise ValueError(f"x must be [{meta.total_rows}, hidden], got {tuple(x.shape)}")
     hidden = int(x.shape[1])
     nf = (hq + 2 * hkv) * D
-    if tuple(w.shape) != (nf, hidden):
+    if w.shape != (nf, hidden):
         raise ValueError(f"w must be [{nf}, {hidden}], got {tuple(w.shape)}")
-    if bias is not None and tuple(bias.shape) != (nf,):
+    if bias is not None and bias.shape != (nf,):
         raise ValueError(f"bias must be [{nf}], got {tuple(bias.shape)}")
-    if rope.dim() != 3 or tuple(rope.shape[1:]) != (D // 2, 2):
+    if rope.dim() != 3 or rope.shape[1:] != (D // 2, 2):
         raise ValueError(f"rope must be [n, {D // 2}, 2], got {tuple(rope.shape)}")
     if not _cache_shapes_ok(k_cache, v_cache, hkv, D):
         raise ValueError("k_cache and v_cache must both be [num_blocks, Hkv, 16, D]")
     if q_out is None:
         q_out = torch.empty((meta.total_rows, hq, D), dtype=torch.bfloat16, device=x.device)
-    elif tuple(q_out.shape) != (meta.total_rows, hq, D):
+    elif q_out.shape != (meta.total_rows, hq, D):
         raise ValueError(f"q_out must be [{meta.total_rows}, {hq}, {D}]")
     _check(_lib.cw_qkv_rope_append(
         _dev(x, torch.bfloat16, "x"), _dev(w, torch.bfloat16, "w"),
@@ -554,13 +563,13 @@ def suffix_prefill_attn(meta: BatchMeta, q: torch.Tensor, k_cache: torch.Tensor,
     if DEBUG_CHECK_COPIES:
         meta.check_device_copies()
     hq, hkv, D = meta.num_q_heads, meta.num_kv_heads, meta.head_dim
-    if tuple(q.shape) != (meta.total_rows, hq, D):
+    if q.shape != (meta.total_rows, hq, D):
         raise ValueError(f"q must be [{meta.total_rows}, {hq}, {D}], got {tuple(q.shape)}")
     if not _cache_shapes_ok(k_cache, v_cache, hkv, D):
         raise ValueError("k_cache and v_cache must both be [num_blocks, Hkv, 16, D]")
     if out is None:
         out = torch.empty_like(q)
-    elif tuple(out.shape) != tuple(q.shape):
+    elif out.shape != q.shape:
         raise ValueError("out must have q's shape")
     _check(_lib.cw_suffix_prefill_attn(
         _dev(q, torch.bfloat16, "q"), _dev(k_cache, torch.bfloat16, "k_cache"),
@@ -578,16 +587,16 @@ def suffix_prefill_append_attn(meta: BatchMeta, q: torch.Tensor, k_new: torch.Te
     """cw_suffix_prefill_append_attn: cw_kv_append and cw_suffix_prefill_attn in
     one launch (same cache image and output); returns out [total_s, Hq, D]."""
     hq, hkv, D = meta.num_q_heads, meta.num_kv_heads, meta.head_dim
-    if tuple(q.shape) != (meta.total_rows, hq, D):
+    if q.shape != (meta.total_rows, hq, D):
         raise ValueError(f"q must be [{meta.total_rows}, {hq}, {D}], got {tuple(q.shape)}")
     for name, t in (("k_new", k_new), ("v_new", v_new)):
-        if tuple(t.shape) != (meta.total_rows, hkv, D):
+        if t.shape != (meta.total_rows, hkv, D):
             raise ValueError(f"{name} must be [{meta.total_rows}, {hkv}, {D}], got {tuple(t.shape)}")
     if not _cache_shapes_ok(k_cache, v_cache, hkv, D):
         raise ValueError("k_cache and v_cache must both be [num_blocks, Hkv, 16, D]")
     if out is None:
         out = torch.empty_like(q)
-    elif tuple(out.shape) != tuple(q.shape):
+    elif out.shape != q.shape:
         raise ValueError("out must have q's shape")
     ph, pd = meta.append_plan(int(k_cache.shape[0]))
     if DEBUG_CHECK_COPIES:
@@ -627,13 +636,13 @@ def suffix_prefill_attn_split(meta: BatchMeta, q: torch.Tensor, k_cache: torch.T
     hq, hkv, D = meta.num_q_heads, meta.num_kv_heads, meta.head_dim
     if num_splits is None:
         num_splits = split_count(meta)
-    if tuple(q.shape) != (meta.total_rows, hq, D):
+    if q.shape != (meta.total_rows, hq, D):
         raise ValueError(f"q must be [{meta.total_rows}, {hq}, {D}], got {tuple(q.shape)}")
     if not _cache_shapes_ok(k_cache, v_cache, hkv, D):
         raise ValueError("k_cache and v_cache must both be [num_blocks, Hkv, 16, D]")
     if out is None:
         out = torch.empty_like(q)
-    elif tuple(out.shape) != tuple(q.shape):
+    elif out.shape != q.shape:
         raise ValueError("out must have q's shape")
     need = split_workspace_bytes(meta, num_splits)
     if workspace is None:
@@ -666,13 +675,13 @@ def suffix_prefill_attn_split_noalloc(meta: BatchMeta, q: torch.Tensor, k_cache:
     hq, hkv, D = meta.num_q_heads, meta.num_kv_heads, meta.head_dim
     if num_splits is None:
         num_splits = split_count(meta)
-    if tuple(q.shape) != (meta.total_rows, hq, D):
+    if q.shape != (meta.total_rows, hq, D):
         raise ValueError(f"q must be [{meta.total_rows}, {hq}, {D}], got {tuple(q.shape)}")
     if not _cache_shapes_ok(k_cache, v_cache, hkv, D):
         raise ValueError("k_cache and v_cache must both be [num_blocks, Hkv, 16, D]")
     if out is None:
         out = torch.empty_like(q)
-    elif tuple(out.shape) != tuple(q.shape):
+    elif out.shape != q.shape:
         raise ValueError("out must have q's shape")
     plan_host, plan_dev = meta.split_plan(int(num_splits))
     _check(_lib.cw_suffix_prefill_attn_split_noalloc(
@@ -689,12 +698,12 @@ def lse_merge(partial_o: torch.Tensor, partial_lse: torch.Tensor, out: torch.Ten
               stream=None) -> torch.Tensor:
     """cw_lse_merge: partial_o fp32 [parts, rows, D], partial_lse fp32 [parts, rows]
     -> out bf16 [rows, D]."""
-    if partial_o.dim() != 3 or partial_lse.dim() != 2 or tuple(partial_lse.shape) != tuple(partial_o.shape[:2]):
+    if partial_o.dim() != 3 or partial_lse.dim() != 2 or partial_lse.shape != partial_o.shape[:2]:
         raise ValueError("partial_o must be [parts, rows, D] and partial_lse [parts, rows]")
     parts, rows, D = partial_o.shape
     if out is None:
         out = torch.empty((rows, D), dtype=torch.bfloat16, device=partial_o.device)
-    elif tuple(out.shape) != (rows, D):
+    elif out.shape != (rows, D):
         raise ValueError(f"out must be [{rows}, {D}]")
     _check(_lib.cw_lse_merge(_dev(partial_o, torch.float32, "partial_o"), _dev(partial_lse, torch.float32, "partial_lse"),
                              parts, rows, D, _dev(out, torch.bfloat16, "out"), _stream(stream)))
