@@ -1,10 +1,10 @@
 """Build-time check of the attention kernels' assembly for untracked loads.
 
-The attention kernel issues some global loads through inline asm so that the
+The attention kernels issue some global loads through inline asm so that the
 compiler does not track them (a tracked load makes it wait for every
 load-to-LDS copy in flight before the first use). Their results are complete
-only after a later `s_waitcnt vmcnt(n)` that covers them, or a step barrier
-(whose wait leaves only the copies issued after them in flight). Until then the
+only after a later `s_waitcnt vmcnt(n)` that covers them (a workgroup barrier
+completes nothing by itself). Until then the
 destination registers must not be read or written: the compiler does not know
 that, so this check walks every control-flow path of the generated gfx9
 assembly from each such load and reports any instruction that touches its
@@ -248,8 +248,6 @@ def hazards(lines: list[str]) -> list[tuple[str, str]]:
                     m = re.search(r'vmcnt\((\d+)\)', text)
                     if m and int(m.group(1)) <= younger:
                         continue
-            elif op == 's_barrier' and not scalar:
-                continue
             elif touches(text) & dst:
                 found.append((insts[li], text))
                 continue
@@ -271,14 +269,20 @@ def functions(asm_text: str, name_part: str) -> dict[str, list[str]]:
     return out
 
 
-def check(asm_text: str, name_part: str = 'suffix_prefill_attn_kernel') -> dict[str, int]:
-    """Untracked loads per checked function; raises on any hazard."""
+KERNELS = ('suffix_prefill_attn_kernel', 'suffix_prefill_stream_kernel')
+
+
+def check(asm_text: str, names: tuple[str, ...] = KERNELS) -> dict[str, int]:
+    """Untracked loads per function whose symbol contains one of `names`; raises
+    on any hazard and when a name matches no function."""
     report = {}
-    for name, lines in functions(asm_text, name_part).items():
-        bad = hazards(lines)
-        if bad:
-            raise RuntimeError(f"{name}: destination of an untracked load used before its wait: {bad[:4]}")
-        report[name] = len(parse(lines)[2])
-    if not report:
-        raise RuntimeError(f"no function matching {name_part!r} in the assembly")
+    for part in names:
+        found = functions(asm_text, part)
+        if not found:
+            raise RuntimeError(f"no function matching {part!r} in the assembly")
+        for name, lines in found.items():
+            bad = hazards(lines)
+            if bad:
+                raise RuntimeError(f"{name}: destination of an untracked load used before its wait: {bad[:4]}")
+            report[name] = len(parse(lines)[2])
     return report

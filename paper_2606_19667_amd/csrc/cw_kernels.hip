@@ -252,13 +252,15 @@ __device__ __forceinline__ u32x2 load_pair_untracked_s(const int32_t* base) {
   return v;
 }
 
-// Brings the 128-byte line holding src (per lane) into L2 with a 4-byte
-// load-to-LDS per lane into lds_addr + 4 l, an area whose bytes nothing reads;
-// completion untracked as above.
-__device__ __forceinline__ void touch_line(const void* src, uint32_t lds_addr) {
+// Lane l's word at src into LDS at lds_addr + 4 l, completion untracked as
+// above (no register is in flight).
+__device__ __forceinline__ void load_word_to_lds(const void* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
                :: "v"(src), "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
+// Brings the 128-byte line holding src (per lane) into L2 with a 4-byte
+// load-to-LDS per lane into lds_addr + 4 l, an area whose bytes nothing reads.
+__device__ __forceinline__ void touch_line(const void* src, uint32_t lds_addr) { load_word_to_lds(src, lds_addr); }
 
 // One load-to-LDS copy: lane l's 16 bytes at base + off + 64 k land at
 // lds + 16 l (k = 0 .. 3). base is wave-uniform (SGPRs), off a per-lane 32-bit
@@ -673,9 +675,11 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
   // nothing else went to memory after them), LDS writes are done, then the
   // workgroup barrier. The empty asm statements keep the compiler from moving
   // memory accesses across the barrier.
-  auto step_barrier = [&](bool keep) __attribute__((always_inline)) {
+  auto step_wait = [&](bool keep) __attribute__((always_inline)) {
     if (keep) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(LPW));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  };
+  auto step_barrier = [&]() __attribute__((always_inline)) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -1133,10 +1137,17 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
       for (int it = 0; it < LPW; ++it)
         if (mine) *reinterpret_cast<u32x4*>(dp + 64 * it) = t[it];
     };
-    auto write_late = [&](int jj) __attribute__((always_inline)) -> bool {
+    // The step's wait goes with it: the stores stay in flight with the step's
+    // copies (`keep`, as for step_barrier). (Each wait sits on the path that
+    // issued what it leaves in flight, where the build's check of the assembly
+    // can count it.)
+    auto write_late = [&](int jj, bool keep) __attribute__((always_inline)) {
       int key0, lo, hi;
       const int dstb = own_span(jj, key0, lo, hi);
-      if (uint32_t(dstb) >= uint32_t(a.num_blocks) || lo != key0 || hi != key0 + kBs) return false;
+      if (uint32_t(dstb) >= uint32_t(a.num_blocks) || lo != key0 || hi != key0 + kBs) {
+        step_wait(keep);
+        return;
+      }
       u32x4 t[LPW];
 #pragma unroll
       for (int it = 0; it < LPW; ++it) t[it] = own_chunk(it);
@@ -1147,17 +1158,8 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
         // wait states before an instruction may write them)
         asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" :: "v"(dp + 64 * it), "v"(t[it]) : "memory");
       }
-      return true;
-    };
-    // The step barrier after write_late's stores: they stay in flight with
-    // the step's copies.
-    auto step_barrier_w = [&](bool keep, bool late) __attribute__((always_inline)) {
-      if (keep && late) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(LPW + NST));
-      else if (keep) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(LPW));
+      if (keep) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(LPW + NST));
       else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
     };
     // Step j < nsteps - 1 at ring position p: current S in sc, next S into sn.
     auto step = [&](int j, f32x16 (&sc)[2], f32x16 (&sn)[2]) __attribute__((always_inline)) {
@@ -1183,8 +1185,9 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
       }
       if (j + 1 >= n_full) mask(sn, (kbeg + j + 1) * kKv);
       mx = phase_b(vbase(p), vf, pb, sn);
-      if (FUSED && j >= own_j0) step_barrier_w(direct, write_late(j));
-      else step_barrier(direct);
+      if (FUSED && j >= own_j0) write_late(j, direct);
+      else step_wait(direct);
+      step_barrier();
       ++p;
     };
     int j = 0;
@@ -1210,8 +1213,9 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
       const bool direct = issue(p + kAhead, true);
       rebase(sa);
       phase_last(vbase(p), sa);
-      if (FUSED && last >= own_j0) step_barrier_w(direct, write_late(last));
-      else step_barrier(direct);
+      if (FUSED && last >= own_j0) write_late(last, direct);
+      else step_wait(direct);
+      step_barrier();
       ++p;
     }
 
@@ -1414,6 +1418,9 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
   // This wave's area after the ring: output staging, and the target of loads
   // whose data nothing reads.
   const uint32_t own_area = lds0 + G::RING + wave * G::STAGING;
+  // The words of an entry to come, word l % 16 at + 4 l (behind the 1 KB that
+  // the loads whose data nothing reads write).
+  const uint32_t own_words = own_area + 1024;
 
   // ---- copy cursor: the entry and step whose blocks this wave copies next.
   // Its state is wave-uniform. The words of the next entry the cursor enters
@@ -1841,11 +1848,13 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
 
     for (int j = 0; j < nsteps; ++j) {
       // ---- softmax interval of step j. In step 0 the next entry's queries are
-      // brought into L2 and the words after it loaded, then the copies of the step two (group 0) or three
+      // brought into L2 and the words of the entry after it into LDS (not into
+      // a register, which would stay in flight over the steps: the compiler may
+      // copy it meanwhile), then the copies of the step two (group 0) or three
       // (group 1) ahead.
       if (__builtin_expect(j == 0, 0)) {
         touch_line(reinterpret_cast<const uint8_t*>(q_row(d1, entry_ok(d1, e_next))) + half * RB / 2, own_area);
-        d2 = load_word_untracked(entry_word_addr(e_next + grid));
+        load_word_to_lds(entry_word_addr(e_next + grid), own_words);
       }
       issue(p + (group1 ? 3 : 2));
 
@@ -1950,6 +1959,10 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
       // (and copies to this wave's own area must not meet the output staged there)
       if (late) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LPW) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      // (the words loaded in step 0, before its copies; the output staged below
+      // overwrites them)
+      d2 = *reinterpret_cast<const int32_t*>(lds + (own_words - lds0) + lane * 4);
+      asm volatile("" : "+v"(d2) :: "memory");
       const float l_tot = sum_pair32(l_run);
       {
         // The output goes through this wave's staging area: a lane holds 4
@@ -2012,9 +2025,8 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
       for (int t = 0; t < DT; ++t) oacc[t] = f32x16{};
       l_run = 0.f;
     }
-    // ---- on to the next entry (d2 landed before the queries were formed)
+    // ---- on to the next entry
     more = entry_ok(d1, e_next);
-    asm volatile("" : "+v"(d2));
     d0 = d1;
     d1 = d2;
     e_cur = e_next;

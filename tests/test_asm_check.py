@@ -41,8 +41,18 @@ def test_every_path_is_followed():
     assert not _hazards(body_ok)
 
 
-def test_barrier_ends_the_window_and_waited_asm_loads_are_tracked():
-    assert not _hazards(LOAD + "\ts_barrier\n\tv_readfirstlane_b32 s6, v10\n")
+def test_bare_barrier_clears_nothing_and_waited_asm_loads_are_tracked():
+    # a barrier orders waves, it does not complete this wave's loads
+    assert _hazards(LOAD + "\ts_barrier\n\tv_readfirstlane_b32 s6, v10\n")
+    assert not _hazards(LOAD + "\ts_waitcnt vmcnt(0)\n\ts_barrier\n\tv_readfirstlane_b32 s6, v10\n")
+    # a step barrier's partial wait covers the load if enough was issued after it
+    copies = "".join(f"\tglobal_load_lds_dwordx4 v{20 + i}, s[4:5]\n" for i in range(4))
+    step = "\ts_waitcnt vmcnt(4)\n\ts_barrier\n\tv_readfirstlane_b32 s6, v10\n"
+    assert not _hazards(LOAD + copies + step)
+    assert _hazards(copies + LOAD + step)
+    # copied to another register over a loop's barriers
+    assert _hazards(LOAD + ".LBB0_1:\n\ts_barrier\n\tv_mov_b32_e32 v30, v10\n\ts_cbranch_scc1 .LBB0_1\n"
+                    "\ts_waitcnt vmcnt(0)\n\tv_readfirstlane_b32 s6, v30\n")
     waited = ("\t;;#ASMSTART\n\tglobal_load_dwordx4 v[10:13], v[0:1], off\n\ts_waitcnt vmcnt(0)\n"
               "\t;;#ASMEND\n\tv_mov_b32_e32 v2, v10\n")
     assert not _hazards(waited)
@@ -54,6 +64,26 @@ def test_check_raises_with_the_function_name():
         asm_check.check(text)
     with pytest.raises(RuntimeError, match="no function"):
         asm_check.check(_fn("\ts_nop 0\n"))
+
+
+def _kernels(bodies):
+    return "".join(_fn(body).replace("k:", f"_{i}{name}_{i}:").replace(".Lfunc_end0", f".Lfunc_end{i}")
+                   for i, (name, body) in enumerate(bodies))
+
+
+def test_check_covers_both_attention_kernels():
+    """Each attention kernel is checked, and the check fails where one is missing
+    from the assembly (a kernel renamed away would otherwise go unchecked)."""
+    good, bad = LOAD + "\ts_waitcnt vmcnt(0)\n", LOAD + "\tv_mov_b32_e32 v2, v10\n"
+    names = ["suffix_prefill_attn_kernel", "suffix_prefill_stream_kernel"]
+    report = asm_check.check(_kernels([(n, good) for n in names] + [(names[1], good)]))
+    assert len(report) == 3 and all(v == 1 for v in report.values())
+    for k, name in enumerate(names):
+        bodies = [(n, bad if n == name else good) for n in names]
+        with pytest.raises(RuntimeError, match=f"_{k}{name}_{k}: destination"):
+            asm_check.check(_kernels(bodies))
+        with pytest.raises(RuntimeError, match=f"no function matching '{name}'"):
+            asm_check.check(_kernels([(n, good) for n in names if n != name]))
 
 
 def test_flag_tests_on_a_lane_mask_follow_both_directions():
