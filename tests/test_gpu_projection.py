@@ -263,3 +263,48 @@ TILES = [
 @pytest.mark.parametrize("name,hq,hkv,D,hidden,plen,slen,kw", TILES, ids=[c[0] for c in TILES])
 def test_tile_edges_and_rounds(name, hq, hkv, D, hidden, plen, slen, kw):
     _ragged(name, hq, hkv, D, hidden, plen, slen, seed=21, **kw).run().check_full()
+
+
+def _many_requests(total, seed):
+    """Suffix lengths 0 to 5, half of them 0, that add up to `total`, with a run of
+    40 empty requests and one of 40 one-row requests."""
+    rng = inputs.rng((seed, 107))
+    s = [1] * min(40, total) + [0] * 40
+    while sum(s) < total:
+        s.append(min(int(rng.integers(-4, 6).clip(0)), total - sum(s)))
+    rng.shuffle(s[:20])
+    return s + [0] * 20, [16 * int(p) for p in rng.integers(0, 4, size=len(s) + 20)]
+
+
+@pytest.mark.parametrize("total", [16, 30, 60, 140, 300, 450, 1200, 2100])
+@pytest.mark.parametrize("D", [64, 128])
+def test_many_short_and_empty_requests(total, D):
+    """Tiles of every size over more requests than the lookup walks one by one."""
+    slen, plen = _many_requests(total, total)
+    _ragged(f"many-requests-{len(slen)}", 28, 4, D, 160, plen, slen, seed=23).run().check_full()
+
+
+def test_empty_requests_cost_little():
+    """The lookup of a token's request does not grow with the empty requests before
+    it: 20,000 of them between two requests take less than 4 times the call's time
+    without them (one after the other they took 25 times as long)."""
+    def call(slen):
+        plen = [16] * len(slen)
+        c = _ragged(f"{len(slen)} requests", 8, 2, 128, 256, plen, slen, seed=24)
+        meta = cw.BatchMeta(c.bt, c.cu, c.plen, c.hq, c.hkv, c.D)
+        rope = torch.from_numpy(cw.rope_table(int(c.pos.max()) + 1, c.D, c.base)).cuda()
+        x, w, kc, vc = c.x.cuda(), c.w.cuda(), c.k0.cuda(), c.v0.cuda()
+        best = math.inf
+        for _ in range(8):   # (a call before it takes the host's check of the batch out of the time)
+            torch.cuda.synchronize()
+            torch.cuda._sleep(5_000_000)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            cw.qkv_rope_append(meta, x, w, rope, kc, vc)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    short, long = call([300, 300]), call([300] + [0] * 20000 + [300])
+    _say(f"two requests {short * 1e3:.1f} us, with 20,000 empty ones between {long * 1e3:.1f} us")
+    assert long < 4 * short
