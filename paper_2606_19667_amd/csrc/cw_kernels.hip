@@ -105,35 +105,63 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(
   const int blk = bt[int64_t(r) * bt_stride + t0 / kBs];
   if (nv <= 0 || blk < 0 || blk >= num_blocks) return;
 
-  // Chunk c = (head, slot, chunk) of the cache block comes from row `slot` of
-  // either tensor, so that a wave's stores are consecutive and no index needs a
-  // division. A thread issues all loads of a batch (K and V) before its stores.
-  // HBM-bound: 16,128 rows of 8 heads of 128 (132 MB, inputs not in a cache)
-  // 31.3 us in source order (stores of four heads' rows per wave), 30.6 now
-  // (4.3 TB/s). Nontemporal accesses: 26.5 there, but slower where the inputs
-  // or the next reader's rows are cached (28.0 against 26.7 before attention,
-  // 4.7 against 4.2 at 512 rows).
+  // A thread issues all loads of a batch (K and V) before its stores.
   const int lg = D == 128 ? 4 : 3;   // log2 of the 16-byte chunks per row and head
   const int64_t src0 = int64_t(cu0 + j0) * hkv << lg;
   const int64_t dst0 = int64_t(blk) * hkv * kBs << lg;
-  const int nk = hkv * kBs << lg;
   constexpr int kBatch = 8;
+  if (nv >= 12) {
+    // Chunk c = (head, slot, chunk) of the cache block comes from row `slot` of
+    // either tensor, so that a wave's stores are consecutive and no index needs
+    // a division; slots past the last row are walked and not stored. 256 units
+    // of 64 heads of 128, us, in source order / so: 16 rows 54.7 / 54.7, 15 rows
+    // 54.6 / 48.9, 12 rows 36.2 / 33.8, 8 rows 24.6 / 25.6, 512 units of 3 rows
+    // 18.2 / 22.8, of 1 row 8.5 / 17.8. 16,128 rows of 8 heads: the
+    // same within noise (30.2 / 29.9 us with the inputs in no cache: 4.4 TB/s,
+    // the rate of a large copy). Nontemporal accesses: 26.5 there, but slower
+    // where the inputs or the next reader's rows are cached (28.0 against 26.7
+    // before attention, 4.7 against 4.2 at 512 rows).
+    const int nk = hkv * kBs << lg;
+    for (int c0 = tid; c0 < nk; c0 += kThreads * kBatch) {
+      u32x4 kr[kBatch], vr[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int c = min(c0 + i * kThreads, nk - 1);
+        const int slot = min((c >> lg) & (kBs - 1), nv - 1);
+        const int64_t o = src0 + (((slot * hkv + (c >> (lg + 4))) << lg) | (c & ((1 << lg) - 1)));
+        kr[i] = k_new[o];
+        vr[i] = v_new[o];
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int c = c0 + i * kThreads;
+        if (c < nk && ((c >> lg) & (kBs - 1)) < nv) {
+          k_cache[dst0 + c] = kr[i];
+          v_cache[dst0 + c] = vr[i];
+        }
+      }
+    }
+    return;
+  }
+  // Fewer rows: chunk c = (slot, head, chunk) of either tensor, in source order,
+  // goes to cache [blk][head][slot][chunk], so that only existing rows are walked.
+  const int nk = nv * hkv << lg;
   for (int c0 = tid; c0 < nk; c0 += kThreads * kBatch) {
     u32x4 kr[kBatch], vr[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-      const int c = min(c0 + i * kThreads, nk - 1);
-      const int slot = min((c >> lg) & (kBs - 1), nv - 1);
-      const int64_t o = src0 + (((slot * hkv + (c >> (lg + 4))) << lg) | (c & ((1 << lg) - 1)));
-      kr[i] = k_new[o];
-      vr[i] = v_new[o];
+      const int64_t c = src0 + min(c0 + i * kThreads, nk - 1);
+      kr[i] = k_new[c];
+      vr[i] = v_new[c];
     }
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const int c = c0 + i * kThreads;
-      if (c < nk && ((c >> lg) & (kBs - 1)) < nv) {
-        k_cache[dst0 + c] = kr[i];
-        v_cache[dst0 + c] = vr[i];
+      if (c < nk) {
+        const int rest = c >> lg, slot = rest / hkv;
+        const int64_t o = dst0 + (((rest - slot * hkv) * kBs + slot) << lg) + (c & ((1 << lg) - 1));
+        k_cache[o] = kr[i];
+        v_cache[o] = vr[i];
       }
     }
   }

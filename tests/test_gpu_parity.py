@@ -141,6 +141,42 @@ def test_kv_append_ragged_bit_exact(hq, hkv, D, nreq):
     _cleanup()
 
 
+@pytest.mark.parametrize("rows", [1, 11, 12, 13])
+def test_kv_append_partial_blocks_bit_exact(rows):
+    """Units on both sides of the row count where the copy order changes."""
+    w = _ragged(48, 24, 64, [rows, 16 + rows, rows], [0, 32, 16], seed=rows)
+    _say(f"kv_append {rows} rows of a block")
+    _append_check(w)
+    _cleanup()
+
+
+def best_us(call, reps=10):
+    """Smallest GPU time of a call, us (the host runs ahead behind a spin)."""
+    best = math.inf
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        torch.cuda._sleep(2_000_000)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+def test_kv_append_of_single_rows_costs_its_rows():
+    """512 one-row suffixes of 64 KV heads take less than twice the time of 8 heads
+    (about 1.4 times; walking every slot of their blocks took 2.7 times)."""
+    def call(heads):
+        db = B.materialize(_ragged(heads, heads, 128, [1] * 512, [0] * 512, seed=5), keep_host=[])
+        return best_us(lambda: cw.kv_append(db.meta, db.k_new, db.v_new, db.k_cache, db.v_cache))
+    few, many = call(8), call(64)
+    _say(f"kv_append, 512 one-row units: 8 heads {few:.1f} us, 64 heads {many:.1f} us")
+    assert many < 2 * few
+    _cleanup()
+
+
 # ------------------------------------------------------------------ attention
 def test_attention_tiny_single_request():
     w = W.tiny_single()
