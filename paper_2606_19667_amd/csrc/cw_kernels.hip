@@ -2069,11 +2069,17 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
 // out = sum_p 2^(lse_p - M) o_p / sum_p 2^(lse_p - M), M = max_p lse_p, where o_p
 // is part p's normalised output and lse_p its base-2 log-sum-exp (-inf for a
 // part with no keys). One thread per row and 8 consecutive elements.
-// Latency-bound: a thread has few bytes to move and its row's weights depend on
-// every part, so the partial outputs of the first CHUNK parts are loaded together
-// with the log-sum-exps, and later ones CHUNK parts at a time. 18,432 rows of 128,
-// 3 parts: 6.76 us with the parts one after the other, 5.93 now; 32,768 rows, 2
-// parts: 8.3 / 7.8 (a branch per part count below 4, so that no part is loaded twice).
+// Latency-bound where rows are few (a row's weights depend on every part), else
+// bound by the read of the parts. The values of part 0, which has keys for every
+// row of a split call, are loaded together with the log-sum-exps, those of later
+// parts CHUNK parts at a time and only where the part has keys (a part that has
+// none costs its log-sum-exp alone), the next parts' log-sum-exps ahead of them.
+// In a captured graph, us, one part after the other / the values of four parts
+// loaded with their log-sum-exps, keys or not / now: 18,432 rows of 128, 3 parts
+// 5.01 / 4.07 / 4.00; 4,096 rows, 4 parts 3.59 / 2.76 / 2.80; 32,768 rows, 4
+// parts 13.3 / 13.1 / 12.5, only one of them with keys 5.08 / 13.0 / 4.49; 8,192
+// rows, 64 parts 68.3 / 54.1 / 54.1, 3 of them with keys 16.7 / 44.2 / 13.5. (A
+// kernel per part count below 4, so that no part is loaded twice.)
 // ---------------------------------------------------------------------------
 template <int CHUNK>
 __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __restrict__ part_o,
@@ -2086,21 +2092,17 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
   if (u >= units) return;
   // (a 64-bit division is far longer than a 32-bit one; the branch is uniform)
   const int64_t row = units <= int64_t(UINT32_MAX) ? int64_t(uint32_t(u) / uint32_t(per_row)) : u / per_row;
-  const float* const src = part_o + u * 8;   // part p's values at p rows d
-  const int64_t stride = rows * d;
+  const f32x4* const src = reinterpret_cast<const f32x4*>(part_o + u * 8);   // part p's values at p stride
+  const int64_t stride = rows * (d / 4);
   f32x4 oa[CHUNK], ob[CHUNK];
-  float lse[CHUNK];
-  auto load = [&](int p0) __attribute__((always_inline)) {
+  float lse[CHUNK], next[CHUNK];
+  auto load_lse = [&](float (&to)[CHUNK], int p0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < CHUNK; ++i) {
-      const int64_t p = min(p0 + i, num_parts - 1);
-      const f32x4* o = reinterpret_cast<const f32x4*>(src + p * stride);
-      lse[i] = part_lse[p * rows + row];
-      oa[i] = o[0];
-      ob[i] = o[1];
-    }
+    for (int i = 0; i < CHUNK; ++i) to[i] = part_lse[int64_t(min(p0 + i, num_parts - 1)) * rows + row];
   };
-  load(0);
+  oa[0] = src[0];
+  ob[0] = src[1];
+  load_lse(lse, 0);
   float m = lse[0];
 #pragma unroll
   for (int i = 1; i < CHUNK; ++i) m = fmaxf(m, lse[i]);
@@ -2108,11 +2110,18 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float wsum = 0.f;
   for (int p0 = 0; p0 < num_parts; p0 += CHUNK) {
-    if (p0 > 0) load(p0);
+    if (p0 + CHUNK < num_parts) load_lse(next, p0 + CHUNK);
+    // (the values of a part without keys are not used, whatever they hold)
+    auto live = [&](int i) __attribute__((always_inline)) { return p0 + i < num_parts && lse[i] != -INFINITY; };
 #pragma unroll
-    for (int i = 0; i < CHUNK; ++i) {
-      // (the values of a part without keys are not used, whatever they hold)
-      if (p0 + i < num_parts && lse[i] != -INFINITY) {
+    for (int i = 0; i < CHUNK; ++i)
+      if ((p0 > 0 || i > 0) && live(i)) {
+        oa[i] = src[(p0 + i) * stride];
+        ob[i] = src[(p0 + i) * stride + 1];
+      }
+#pragma unroll
+    for (int i = 0; i < CHUNK; ++i)
+      if (live(i)) {
         const float w = __builtin_amdgcn_exp2f(lse[i] - m);
         wsum += w;
 #pragma unroll
@@ -2121,7 +2130,8 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
           acc[4 + e] = fmaf(w, ob[i][e], acc[4 + e]);
         }
       }
-    }
+#pragma unroll
+    for (int i = 0; i < CHUNK; ++i) lse[i] = next[i];
   }
   const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
   const u32x4 o{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),

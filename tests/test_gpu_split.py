@@ -3,6 +3,7 @@ the fp64 oracle (same bars as the plain attention: max-abs <= 2e-2, mean-abs
 <= 2e-3 against the unrounded fp64 result)."""
 import numpy as np
 import pytest
+import test_gpu_parity as GP
 import torch
 
 from oracle import attention as OA
@@ -84,6 +85,21 @@ def test_lse_merge_ignores_values_of_empty_parts(parts):
     got = cw.lse_merge(o.cuda(), lse.cuda())
     torch.cuda.synchronize()
     _check(got.float().cpu().numpy(), expect, f"lse_merge with NaN in empty parts, parts={parts}")
+
+
+@pytest.mark.parametrize("parts,live", [(4, 1), (16, 2)])
+def test_lse_merge_reads_no_values_of_empty_parts(parts, live):
+    """A merge whose later parts have no keys takes less than half the time of one
+    whose parts all have some (reading their values took as long)."""
+    rows, d = 131072, 128
+    o = torch.zeros((parts, rows, d), dtype=torch.float32, device="cuda")
+    lse = torch.zeros((parts, rows), dtype=torch.float32, device="cuda")
+    out = torch.empty((rows, d), dtype=torch.bfloat16, device="cuda")
+    full = GP.best_us(lambda: cw.lse_merge(o, lse, out))
+    lse[live:] = -float("inf")
+    few = GP.best_us(lambda: cw.lse_merge(o, lse, out))
+    print(f"lse_merge of {parts} parts: {full:.1f} us, {live} with keys {few:.1f} us", flush=True)
+    assert few < full / 2
 
 
 @pytest.mark.parametrize("splits", [1, 2, 4, 7])
