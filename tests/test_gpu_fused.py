@@ -98,12 +98,14 @@ def test_fused_ragged_shapes(hq, hkv, D):
     GP._cleanup()
 
 
-def test_fused_out_of_pool_entries():
+@pytest.mark.parametrize("kernel", ["attn", "stream"])
+def test_fused_out_of_pool_entries(kernel):
     """Table entries -1 and >= num_blocks in prefix and suffix blocks: writes
     dropped, reads as zeros, as in the two calls."""
-    w = GP._oop_workload()
+    w = GP._oop_workload(kernel)
     GP._say(f"fused out-of-pool entries {w.name}")
     seq, fus, out_s, out_f, img = _pair(w, table=GP._corrupt_table, keep_host=[])
+    assert f"suffix_prefill_{kernel}_kernel" in GP.kernels(lambda: _fused(fus))[-1]
     _check_same(seq, fus, out_s, out_f, img, w.name + " (out-of-pool entries)")
     GP._cleanup()
 
@@ -167,10 +169,6 @@ def test_fused_runner_matches_sequential_calls_bitwise():
     GP._cleanup()
 
 
-def _steps(meta):
-    return int(meta.plan_host[cw.HDR_WORK]) - meta.num_tiles
-
-
 LONG_S = [1, 15, 16, 17, 300, 0, 33, 64]
 LONG_P = [1008, 1024, 2048, 1600, 1024, 32, 1504, 912]
 
@@ -189,13 +187,25 @@ def test_long_entries_match_oracle_and_short_batch_bits(hq, hkv):
     assert torch.equal(_fused(fus).view(torch.int16), out_s.view(torch.int16))
     assert torch.equal(fus.k_cache.view(torch.int16), seq.k_cache.view(torch.int16))
     assert torch.equal(fus.v_cache.view(torch.int16), seq.v_cache.view(torch.int16))
-    steps, tiles = _steps(seq.meta), seq.meta.num_tiles
-    assert steps >= 17 * tiles
-    n = 400   # suffix of an extra request without a prefix: at most seven steps a tile
-    extra = -(-2 * tiles * 256 // (n * hq)) + 2
+    assert "suffix_prefill_stream_kernel" in GP.kernels(lambda: GP._run(seq))[-1]
+    assert "suffix_prefill_stream_kernel" in GP.kernels(lambda: _fused(fus))[-1]
+    n = 64   # suffix of an extra request without a prefix: one step a tile
+    extra = -(-5 * seq.meta.num_tiles * 256 // (n * hq)) + 2
     w2 = GP._ragged(hq, hkv, 128, LONG_S + [n] * extra, LONG_P + [0] * extra, seed=hq + 11)
     both = B.materialize(w2, keep_host=[])
-    assert _steps(both.meta) < 14 * both.meta.num_tiles
     out_b = GP._run(both)
+    assert "suffix_prefill_attn_kernel" in GP.kernels(lambda: GP._run(both))[-1]
     assert torch.equal(out_b[:out_s.shape[0]].view(torch.int16), out_s.view(torch.int16))
+    GP._cleanup()
+
+
+@pytest.mark.parametrize("kernel", ["attn", "stream"])
+def test_fused_with_rising_scores(kernel):
+    """The softmax base moves with the scores in the fused kernels too."""
+    n, P = (8, [320, 512, 64]) if kernel == "attn" else (1, [1600, 1024, 1504])
+    w = GP._ragged(8, 2, 128, [300, 17, 130] * n, P * n, seed=3)
+    seq, fus = (GP.rising_scores(B.materialize(w, keep_host=[])) for _ in range(2))
+    out = GP._run(seq)
+    assert f"suffix_prefill_{kernel}_kernel" in GP.kernels(lambda: GP._run(seq))[-1]
+    assert torch.equal(_fused(fus).view(torch.int16), out.view(torch.int16))
     GP._cleanup()

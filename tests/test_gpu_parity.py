@@ -12,6 +12,7 @@ import math
 import numpy as np
 import pytest
 import torch
+from torch.profiler import ProfilerActivity, profile
 
 from oracle import attention as OA
 from oracle import paged as OP
@@ -34,6 +35,16 @@ def _run(db):
     out = cw.suffix_prefill_attn(db.meta, db.q, db.k_cache, db.v_cache, db.scale)
     torch.cuda.synchronize()
     return out
+
+
+def kernels(call):
+    """Names of the kernels that `call` launches."""
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    names = [e.name for e in prof.events() if "_kernel" in e.name]
+    assert names, "the profiler reported no kernel"
+    return names
 
 
 def _bits(t):
@@ -357,9 +368,10 @@ def _corrupt_table(db):
     return bt
 
 
-def _oop_workload():
+def _oop_workload(kernel="attn"):
+    """Entries of few steps (the interleaved kernel) or of many (the alternating one)."""
     S = [40, 70, 100]
-    P = [32, 64, 96]
+    P = [32, 64, 96] if kernel == "attn" else [1600, 1664, 1712]
     return _ragged(8, 2, 128, S, P, seed=77)
 
 
@@ -380,14 +392,16 @@ def test_kv_append_drops_out_of_pool_writes_bit_exact():
     _cleanup()
 
 
-def test_attention_reads_out_of_pool_blocks_as_zeros():
+@pytest.mark.parametrize("kernel", ["attn", "stream"])
+def test_attention_reads_out_of_pool_blocks_as_zeros(kernel):
     """Against the oracle with the logical K/V rows of every out-of-pool block
     of a request zeroed (prefix and suffix blocks alike)."""
-    w = _oop_workload()
+    w = _oop_workload(kernel)
     db = B.materialize(w)
     db = _with_table(db, _corrupt_table(db))
     _say(f"attention out-of-pool entries {w.name}")
     out = _run(db)
+    assert f"suffix_prefill_{kernel}_kernel" in kernels(lambda: _run(db))[-1]
     nb = db.sched.num_blocks
     outs, exps = [], []
     for r in range(w.batch):
@@ -403,19 +417,81 @@ def test_attention_reads_out_of_pool_blocks_as_zeros():
 
 
 # ------------------------------------------------------------------ plan binding on the device
-def test_device_plan_of_another_batch_computes_nothing():
-    """A device plan whose header fingerprint is not the validated batch's: the
-    kernel writes nothing (the host copy passed validation)."""
-    w = W.tiny_single()
+@pytest.mark.parametrize("kernel", ["attn", "stream"])
+def test_device_plan_of_another_batch_computes_nothing(kernel):
+    """A device plan whose header fingerprint, or whose first entries' check
+    words, are not the validated batch's: the kernel writes nothing there (the
+    host copy passed validation)."""
+    w = W.tiny_single() if kernel == "attn" else _ragged(8, 2, 128, [40, 70], [1600, 2000], seed=78)
     db = B.materialize(w, keep_host=[])
     cw.kv_append(db.meta, db.k_new, db.v_new, db.k_cache, db.v_cache)
-    db.meta.plan[2] += 1                        # fingerprint word of the device copy only
     sentinel = torch.full_like(db.q, 7.0)
-    cw.suffix_prefill_attn(db.meta, db.q, db.k_cache, db.v_cache, db.scale, out=sentinel)
-    torch.cuda.synchronize()
+
+    def call():
+        cw.suffix_prefill_attn(db.meta, db.q, db.k_cache, db.v_cache, db.scale, out=sentinel)
+    db.meta.plan[2] += 1                        # fingerprint word of the device copy only
+    assert f"suffix_prefill_{kernel}_kernel" in kernels(call)[-1]
     assert torch.all(sentinel == 7.0)
     db.meta.plan[2] -= 1
-    cw.suffix_prefill_attn(db.meta, db.q, db.k_cache, db.v_cache, db.scale, out=sentinel)
+    # the entries of a fused plan of the same batch: another fingerprint, other check words
+    own = db.meta.plan.clone()
+    other = db.meta.append_plan(db.sched.num_blocks)[1]
+    body = slice(cw.PLAN_HEADER, cw.PLAN_HEADER + cw.PLAN_ENTRY * int(db.meta.plan_host[cw.HDR_ENTRIES]))
+    db.meta.plan[body] = other[body]
+    call()
     torch.cuda.synchronize()
-    assert not torch.all(sentinel == 7.0)
+    assert torch.all(sentinel == 7.0)
+    # the first entry of every queue is the batch's, the rest are not: one entry a queue
+    first = slice(cw.PLAN_HEADER, cw.PLAN_HEADER + cw.PLAN_ENTRY)
+    db.meta.plan[first] = own[first]
+    call()
+    torch.cuda.synchronize()
+    written = int((sentinel != 7.0).any(-1).sum())
+    ent = cw.plan_entries(db.meta.plan_host)[0]
+    assert written == int(ent[cw.ENT_NVALID]) * w.num_q_heads // w.num_kv_heads
+    db.meta.plan.copy_(own)
+    call()
+    torch.cuda.synchronize()
+    assert (sentinel != 7.0).any(-1).all()
+    _cleanup()
+
+
+# ------------------------------------------------------------------ rising scores
+def rising_scores(db, seed=0):
+    """Gives every key the value 1.5 x (its 64-key step) in dimension 0 and every
+    query row one of 64, 20, 0, -64 there: in base 2 a row's scores then rise by
+    up to 12 or 4 a step, stay, or fall, so that its base moves in every step, in
+    every third, or never."""
+    g = torch.Generator().manual_seed(seed)
+    dev = db.q.device
+    vals = torch.tensor([64.0, 20.0, 0.0, -64.0], dtype=torch.bfloat16)
+    for r in range(db.workload.batch):
+        c0, c1 = int(db.sched.cu_suffix[r]), int(db.sched.cu_suffix[r + 1])
+        P, L = int(db.sched.prefix_len[r]), int(db.sched.prefix_len[r]) + c1 - c0
+        pos = torch.arange(L)
+        k0 = (1.5 * (pos // 64)).to(torch.bfloat16)
+        q0 = vals[torch.randint(0, 4, (c1 - c0, db.q.shape[1]), generator=g)]
+        db.q[c0:c1, :, 0] = q0.to(dev)
+        db.k_new[c0:c1, :, 0] = k0[P:, None].to(dev)
+        ids = torch.from_numpy(db.sched.block_table[r].astype(np.int64))[pos[:P] // 16].to(dev)
+        db.k_cache[ids, :, (pos[:P] % 16).to(dev), 0] = k0[:P, None].to(dev)
+        if db.logical_k[r] is not None:
+            db.logical_k[r][:, :, 0] = k0[:, None]
+            db.q_host[r][:, :, 0] = q0
+    return db
+
+
+@pytest.mark.parametrize("kernel", ["attn", "stream"])
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (28, 4)])
+def test_attention_with_rising_scores(kernel, hq, hkv):
+    """The softmax base moves with the scores (in both kernels). Tolerances as
+    elsewhere: a row's rounded query scales all its scores by the same factor
+    1 + 2^-9, at most 0.02 in the exponent between neighbouring steps."""
+    S, P = ([300, 17, 130], [320, 512, 64]) if kernel == "attn" else ([300, 17, 130], [1600, 1024, 1504])
+    w = _ragged(hq, hkv, 128, S * (1 if kernel == "stream" else 8), P * (1 if kernel == "stream" else 8), seed=hq)
+    db = rising_scores(B.materialize(w))
+    _say(f"attention with rising scores {w.name}")
+    out = _run(db)
+    assert f"suffix_prefill_{kernel}_kernel" in kernels(lambda: _run(db))[-1]
+    _compare_full(db, out)
     _cleanup()
