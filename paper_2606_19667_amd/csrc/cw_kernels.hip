@@ -2181,7 +2181,7 @@ namespace {
 struct AttnLaunch {
   AttnArgs args;
   int32_t grid = 0, splits = 1;
-  int64_t steps = 0, tiles = 0;   // 64-key steps and tiles of an unsplit plan
+  int64_t steps = 0, queue_len = 0;   // of an unsplit plan: 64-key steps, entries of the longest queue
   int64_t rows = 0;
 };
 cw_status check_attn(const char* what, const void* q, const void* k_cache, const void* v_cache,
@@ -2236,23 +2236,35 @@ cw_status check_attn(const char* what, const void* q, const void* k_cache, const
   a.num_blocks = num_blocks;
   a.c_log2 = softmax_scale * 1.4426950408889634f;
   // (the header's work counts the steps of every entry and one more)
-  L->tiles = cw::count_tiles(cu_suffix_host, batch, num_kv_heads, a.per_tile);
-  L->steps = plan_host[cw::kHdrWork] - L->tiles;
+  L->steps = plan_host[cw::kHdrWork] - cw::count_tiles(cu_suffix_host, batch, num_kv_heads, a.per_tile);
+  L->queue_len = plan_host[cw::kHdrQueueLen];
   return CW_OK;
 }
 
-// Whether an unsplit call takes the alternating kernel; both give the same bits.
-// It gains on every step and pays at an entry's end, which takes the two groups
-// one after the other. Both in turn on one card, us, interleaved / alternating,
-// by mean steps of an entry (entries): 64 (120) 112 / 101, 43 (680) 226 / 218, 26
-// (192) 53.5 / 51.4, 19 (328) 63.3 / 63.0; 14 (2,080: 115 steps a queue) 244 /
-// 241, 14 (512: 29 a queue) 67.4 / 66.4, 16 (296: 19 a queue) 54.5 / 55.2; 8
-// (528) 54 / 56, 5 (616) 46.7 / 49.7. Hence 17 steps an entry, or 14 where the
-// queues are long as well. At head_dim 64 the products are half as long and the
-// softmax is not: 13 (276) 30.1 / 33.5.
+// Whether an unsplit or fused call takes the alternating kernel; both give the
+// same bits. It gains on every step and pays at an entry's end, which takes the
+// two groups one after the other. The longest queue bounds a call, so its
+// entries count, not the mean: with 128 one-step requests beside one of 47
+// tiles, eight queues hold most of the short entries. The line lies where the
+// two met, at mean steps a queue against entries of the longest queue, over 96
+// batches (uniform, random, a long request among short ones, retrieval traces).
+// Both in turn on one card, us, interleaved / alternating, unfused and fused, at
+// steps a queue (entries of the longest):
+//    8.5 (1)  31.7 / 30.8   34.2 / 33.6      34 (4)  85.9 / 89.6   91.3 / 95.3
+//   16.5 (1)  41.6 / 39.7   44.6 / 42.9      58 (4)   126 / 127     134 / 134
+//   14.6 (2)  46.3 / 47.9   49.3 / 50.8      66 (4)   141 / 141     149 / 150
+//   23.6 (2)  69.4 / 68.6   73.1 / 72.7      98 (4)   198 / 195     208 / 205
+//   32.6 (2)  93.0 / 90.4   98.2 / 95.6     274 (4)   524 / 495     553 / 516
+//   84 (9)     175 / 189     182 / 197      112 (8)   254 / 255     270 / 268
+//  175 (9)     358 / 339     373 / 352      404 (16)  801 / 770     842 / 808
+// The chosen kernel was at most 1.2 % slower than the other, but for one batch
+// (18.5 steps, 2 entries: 51.3 / 49.3).
+// At head_dim 64 the products are half as long and the softmax is not: 41 (2)
+// 53.4 / 55.7 and 57.7 / 63.5, 272 (5) 319 / 320 and 337 / 353, 642 (4) 650 / 655
+// and 704 / 721.
 bool long_entries(int head_dim, const AttnLaunch& L) {
   if (head_dim != 128) return false;
-  return L.steps >= 17 * L.tiles || (L.steps >= 14 * L.tiles && L.steps >= 28 * int64_t(L.grid));
+  return L.steps >= std::min<int64_t>(16 * L.queue_len - 8, 14 * L.queue_len) * L.grid;
 }
 
 template <bool SPLIT, bool FUSED = false>

@@ -209,3 +209,30 @@ def test_fused_with_rising_scores(kernel):
     assert f"suffix_prefill_{kernel}_kernel" in GP.kernels(lambda: GP._run(seq))[-1]
     assert torch.equal(_fused(fus).view(torch.int16), out.view(torch.int16))
     GP._cleanup()
+
+
+ROUTES = [
+    # (query heads, KV heads, head_dim, suffixes, prefixes, kernel)
+    (32, 8, 128, [512] * 16, [2048] * 16, "stream"),
+    (32, 8, 128, [512] * 16, [128] * 16, "attn"),
+    (32, 8, 128, [1024], [1024], "stream"),
+    (32, 8, 128, [40], [16], "attn"),
+    # long entries on average, but queues of many short ones beside them
+    (32, 8, 128, [64] * 64 + [3000], [0] * 64 + [2000], "attn"),
+    (32, 8, 128, [64] * 128 + [3000], [0] * 128 + [2000], "attn"),
+    (32, 8, 128, [64] * 128 + [4000], [0] * 128 + [6000], "attn"),
+    (32, 8, 128, [64] * 16 + [3000], [0] * 16 + [2000], "stream"),
+    (16, 4, 64, [512] * 4, [4096] * 4, "attn"),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,D,S,P,kernel", ROUTES)
+def test_kernel_follows_the_longest_queue(hq, hkv, D, S, P, kernel):
+    """Which kernel a batch takes; 128 one-step requests beside a request of long
+    entries took 22 % longer with the kernel chosen by the mean entry."""
+    w = GP._ragged(hq, hkv, D, S, P, seed=1)
+    db = B.materialize(w, keep_host=[], gen_device="cuda")
+    GP._say(f"route {w.name}")
+    assert f"suffix_prefill_{kernel}_kernel" in GP.kernels(lambda: GP._run(db))[-1]
+    assert f"suffix_prefill_{kernel}_kernel" in GP.kernels(lambda: _fused(db))[-1]
+    GP._cleanup()
