@@ -428,7 +428,6 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
   // Both tensors are staged chunk-major: 16-byte chunk c of key row r of a
   // block at c 256 + r' 16, with r' = r for K and r' = r ^ 4 (c % 4) for V, so
   // copy i (chunks 4 i .. 4 i + 3) brings lane l the chunk 4 i + l / 16 of key
-  // ckey (below).
   // ckey (below). Copy i adds 64 i (its immediate offset) to the lane's base:
   // off_c for a cache block (rows RB apart), off_n for rows of k_new / v_new
   // (rows Hkv RB apart).
@@ -1390,9 +1389,10 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
 // in its softmax(s-2) and are waited for at the end of its products(s-1), which
 // runs beside group 0's softmax(s).
 // ---------------------------------------------------------------------------
-template <int D, bool FUSED>
+template <bool FUSED>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void suffix_prefill_stream_kernel(const AttnArgs a) {
+  constexpr int D = 128;   // (at 64 it is never the faster kernel)
   using G = AttnGeom<D>;
   constexpr int KS = G::KS, DT = G::DT, RB = G::RB, LPW = G::LPW;
   constexpr int KTILE = G::KTILE, BLK = G::BLK, VTILE = G::VTILE, KREG = G::KREG;
@@ -1425,7 +1425,6 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
   // Both tensors are staged chunk-major: 16-byte chunk c of key row r of a
   // block at c 256 + r' 16, with r' = r for K and r' = r ^ 4 (c % 4) for V, so
   // copy i (chunks 4 i .. 4 i + 3) brings lane l the chunk 4 i + l / 16 of key
-  // ckey (below).
   // ckey (below). Copy i adds 64 i (its immediate offset) to the lane's base:
   // off_c for a cache block (rows RB apart), off_n for rows of k_new / v_new
   // (rows Hkv RB apart).
@@ -1704,20 +1703,15 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
     const u32x4* qp = q_row(d, exists) + half;
     const bool ok = has_row(d);
     u32x4 raw[KS];
-    if constexpr (KS == 8)
-      asm volatile("global_load_dwordx4 %0, %8, off\n\tglobal_load_dwordx4 %1, %8, off offset:32\n\t"
-                   "global_load_dwordx4 %2, %8, off offset:64\n\tglobal_load_dwordx4 %3, %8, off offset:96\n\t"
-                   "global_load_dwordx4 %4, %8, off offset:128\n\tglobal_load_dwordx4 %5, %8, off offset:160\n\t"
-                   "global_load_dwordx4 %6, %8, off offset:192\n\tglobal_load_dwordx4 %7, %8, off offset:224\n\t"
-                   "s_waitcnt vmcnt(0)"
-                   : "=&v"(raw[0]), "=&v"(raw[1]), "=&v"(raw[2]), "=&v"(raw[3]), "=&v"(raw[KS - 4]),
-                     "=&v"(raw[KS - 3]), "=&v"(raw[KS - 2]), "=&v"(raw[KS - 1])
-                   : "v"(qp) : "memory");
-    else
-      asm volatile("global_load_dwordx4 %0, %4, off\n\tglobal_load_dwordx4 %1, %4, off offset:32\n\t"
-                   "global_load_dwordx4 %2, %4, off offset:64\n\tglobal_load_dwordx4 %3, %4, off offset:96\n\t"
-                   "s_waitcnt vmcnt(0)"
-                   : "=&v"(raw[0]), "=&v"(raw[1]), "=&v"(raw[2]), "=&v"(raw[3]) : "v"(qp) : "memory");
+    static_assert(KS == 8, "eight loads of 16 bytes");
+    asm volatile("global_load_dwordx4 %0, %8, off\n\tglobal_load_dwordx4 %1, %8, off offset:32\n\t"
+                 "global_load_dwordx4 %2, %8, off offset:64\n\tglobal_load_dwordx4 %3, %8, off offset:96\n\t"
+                 "global_load_dwordx4 %4, %8, off offset:128\n\tglobal_load_dwordx4 %5, %8, off offset:160\n\t"
+                 "global_load_dwordx4 %6, %8, off offset:192\n\tglobal_load_dwordx4 %7, %8, off offset:224\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(raw[0]), "=&v"(raw[1]), "=&v"(raw[2]), "=&v"(raw[3]), "=&v"(raw[4]),
+                   "=&v"(raw[5]), "=&v"(raw[6]), "=&v"(raw[7])
+                 : "v"(qp) : "memory");
 #pragma unroll
     for (int s = 0; s < KS; ++s)
       qf[s] = ok ? scale_bf16x8(raw[s], a.c_log2) : __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
@@ -1768,7 +1762,7 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
   auto kbase = [&](int pp) { return k_off + (pp & (kStages - 1)) * KTILE; };
   auto vbase = [&](int pp) { return (pp & (kStages - 1)) * VTILE; };
   // Operands in flight ahead of their MFMA.
-  constexpr int RA = DT == 4 ? 6 : 4;
+  constexpr int RA = 6;
   constexpr int NPV = 4 * DT, NQK = 2 * KS, N = NPV + NQK;
   bf16x8 op[RA];
   auto read_op = [&](int pp, int i) __attribute__((always_inline)) {
@@ -1915,11 +1909,8 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
         mx = max_pair32(fmaxf(x, y));
       }
       if (__builtin_expect(j == 0, 0)) {
-        // The first step's exact row maximum is the base. Finite when the run's
-        // first step has a visible key for this row (always so for the first
-        // run: key 0 is visible to every row). A row that sees no key of the
-        // run's first step sees none of its later steps either (they hold
-        // higher keys), so any base serves it.
+        // The first step's exact row maximum is the base. (Key 0 is visible to
+        // every row, so it is finite unless every score of the step is -inf.)
         const float m0 = mx == -INFINITY ? 0.f : mx;
 #pragma unroll
         for (int h = 0; h < 2; ++h) sc[h] -= m0;
@@ -2271,7 +2262,7 @@ template <bool SPLIT, bool FUSED = false>
 void launch_attn(int head_dim, const AttnLaunch& L, hipStream_t s) {
   if constexpr (!SPLIT) {
     if (long_entries(head_dim, L)) {
-      hipLaunchKernelGGL((suffix_prefill_stream_kernel<128, FUSED>), dim3(unsigned(L.grid)), dim3(kAttnThreads), 0, s,
+      hipLaunchKernelGGL(suffix_prefill_stream_kernel<FUSED>, dim3(unsigned(L.grid)), dim3(kAttnThreads), 0, s,
                          L.args);
       return;
     }
