@@ -475,7 +475,8 @@ cw_status cw_rope_table(int32_t n_positions, int32_t head_dim, double base, floa
  *     of KV head g, blk = block_table[r][p / 16]; a block id outside
  *     [0, num_blocks) is skipped (nothing written).
  * Every output is rounded once, RNE, to bf16; every other cache byte keeps
- * its value.
+ * its value. The sums over hidden are fp32 in one order, whatever the batch: a
+ * row's results do not depend on the other rows of the call.
  *   x       device bf16 [total_s, hidden], rows in request order
  *   w       device bf16 [(Hq + 2 Hkv) head_dim, hidden] (one row per feature)
  *   bias    device bf16 [(Hq + 2 Hkv) head_dim], or NULL for none

@@ -12,7 +12,7 @@
 //   q -> q_out [T, Hq, D];  k -> K cache [blk][g][slot][d];
 //   v -> V cache [blk][g][slot][d]
 //
-// Eight tile shapes serve batches from one token to tens of thousands (kShapes:
+// Seven tile shapes serve batches from one token to tens of thousands (kShapes:
 // which, and why). The largest, persistent workgroups of 8 wavefronts, one per
 // CU, walking tiles of 256 features x 256 tokens:
 //  * The product is formed as C^T = W x^T with v_mfma_f32_16x16x32_bf16:
@@ -50,8 +50,8 @@
 // Smaller tiles (below) keep this staging, operand layout and epilogue.
 // Bound: the matrix pipe under the card's power limit (the clock falls to about
 // 1.7 GHz on random data, 2.39 on zeros). T = 16,128, hidden 4,096, 6,144
-// features (812 GFLOP): 579 us, 1.40 PFLOP/s; with one barrier per step for all
-// waves, a 2-stage ring and one workgroup per tile it took 678 us (same card).
+// features (812 GFLOP), back to back: 567 us, 1.43 PFLOP/s; with one barrier per
+// step for all waves, a 2-stage ring and one workgroup per tile 672 us (same card).
 // A tile takes 138 k cycles for its 64 steps (131 k of them products of the two
 // waves of a SIMD) and 9 k for its epilogue.
 
@@ -282,8 +282,8 @@ __device__ __forceinline__ void store_results(const QkvArgs& a, f32x4 (&acc)[2 *
         float b0 = acc[FH + (e >> 1)][tb][(e & 1) * 2], b1 = acc[FH + (e >> 1)][tb][(e & 1) * 2 + 1];
         if constexpr (kRotate) {
           const f32x4 r = cs[e];   // cos, sin of two rotary indices
-          const float ra = a0 * r[0] - b0 * r[1], rb = b0 * r[0] + a0 * r[1];
-          const float sa = a1 * r[2] - b1 * r[3], sb = b1 * r[2] + a1 * r[3];
+          const float ra = fmaf(a0, r[0], -(b0 * r[1])), rb = fmaf(b0, r[0], a0 * r[1]);
+          const float sa = fmaf(a1, r[2], -(b1 * r[3])), sb = fmaf(b1, r[2], a1 * r[3]);
           a0 = ra;
           b0 = rb;
           a1 = sa;
@@ -318,6 +318,14 @@ __device__ __forceinline__ void tile_origin(const QkvArgs& a, int L, int tile_f,
   const int rem = L - grp * kGroupF * a.n_ttiles;
   t0 = (rem / gf) * tile_t;
   f0 = (grp * kGroupF + rem % gf) * tile_f;
+}
+
+// Byte offset in a row of W or x of plane p (64 hidden) of `planes`. Past the last
+// plane: that plane again, which nothing uses. A last plane of 32 hidden is moved
+// back to the row's last 64.
+__device__ __forceinline__ int64_t plane_offset(int p, int planes, bool half_last) {
+  const int q = min(p, planes - 1);
+  return int64_t(q) * kRow - ((half_last && q == planes - 1 && q > 0) ? kRow / 2 : 0);
 }
 
 template <int D>
@@ -492,30 +500,22 @@ void qkv_rope_append_kernel(const QkvArgs a) {
 
 // ---------------------------------------------------------------------------
 // Fewer tokens: one smaller tile per workgroup, so that more CUs work on the
-// batch. Same staging, operand layout and alternation of two wave groups as
-// above, with one reading and one product interval (both k-steps) per step.
-//  * KSPLIT false: 256 features x 128 tokens. Wave (wf, group) owns 64 features
-//    and 64 tokens. A ring of three stages (W and x rows of a step).
-//  * KSPLIT true: 128 features x 128 tokens; the groups share the tile and take
-//    alternate steps of 64 hidden, each with a five-slot ring of its own, and
-//    add their sums at the end (each group finishes half of the tokens).
+// batch. Same staging, operand layout and epilogue as above, and the same order
+// of every sum: each accumulator takes the steps of 32 hidden one after the other
+// in one wave, in every kernel of this file, so a token's results do not depend
+// on the tile that computes it, nor on the rest of its batch.
+//
+// 256 features x 128 tokens, alternating wave groups as above with one reading
+// and one product interval (both k-steps) per step. Wave (w4, gr) owns 64
+// features and 64 tokens. A ring of three stages (W and x rows of a step).
 // ---------------------------------------------------------------------------
-template <bool KSPLIT>
-struct TileGeom {
-  static constexpr int TF = KSPLIT ? 128 : 256, TT = 128;
-  static constexpr int W_BYTES = TF * kRow, X_BYTES = TT * kRow;
-  static constexpr int RING = KSPLIT ? 5 * W_BYTES : 3 * (W_BYTES + X_BYTES);   // per group / shared
-  static constexpr int LDS = KSPLIT ? 2 * RING : RING;
-  static constexpr int EXCHANGE = 8 * 8192;   // KSPLIT: the sums handed to the other group
-  static_assert(!KSPLIT || W_BYTES == X_BYTES, "slots hold W and x rows in turn");
-  static_assert(LDS <= 160 * 1024 && EXCHANGE + 8 * 4096 <= LDS, "LDS of one CU");
-};
-
-template <int D, bool KSPLIT>
+template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qkv_tile_kernel(const QkvArgs a) {
-  using G = TileGeom<KSPLIT>;
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
+  constexpr int TF = 256, TT = 128;
+  constexpr int W_BYTES = TF * kRow, STAGE = W_BYTES + TT * kRow;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[3 * STAGE];
+  static_assert(3 * STAGE <= 160 * 1024, "LDS of one CU");
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   const int tile = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
   if (tile >= a.n_ftiles * a.n_ttiles) return;
@@ -525,59 +525,45 @@ void qkv_tile_kernel(const QkvArgs a) {
   const int w4 = wave & 3, gr = wave >> 2;
 
   int f_own, t_own;
-  tile_origin(a, tile, G::TF, G::TT, f_own, t_own);
+  tile_origin(a, tile, TF, TT, f_own, t_own);
   // (a tile past the last row of W or x is moved back, as above)
-  const int f0 = min(f_own, max(a.n_feat - G::TF, 0)), t0 = min(t_own, max(a.T - G::TT, 0));
+  const int f0 = min(f_own, max(a.n_feat - TF, 0)), t0 = min(t_own, max(a.T - TT, 0));
 
-  // ---- staging: planes of 64 hidden, one per step (KSPLIT: per step and group)
+  // ---- staging: planes of 64 hidden, one per step
   const int64_t hb = int64_t(a.hidden) * 2;
-  const int planes = (a.hidden + kStep - 1) / kStep;
-  const int nk = KSPLIT ? (planes + 1) / 2 : planes;
+  const int nk = (a.hidden + kStep - 1) / kStep;
   const bool half_last = (a.hidden % kStep) != 0;
   const uint8_t* const wb = a.w + int64_t(f0) * hb;
   const uint8_t* const xb = a.x + int64_t(t0) * hb;
-  constexpr int NX = KSPLIT ? 4 : 2;             // x copies per wave and step
-  const int rw0 = KSPLIT ? 32 * w4 : 32 * wave;  // this wave's W and x rows
-  const int rx0 = KSPLIT ? 32 * w4 : 16 * wave;
-  uint32_t offw[4], offx[NX];
+  uint32_t offw[4], offx[2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = rw0 + 8 * i + (lane >> 3);
+    const int row = 32 * wave + 8 * i + (lane >> 3);
     int c = ((lane & 7) ^ row_swz(row)) * 16;
     if (a.hidden < kStep) c &= ~64;
     offw[i] = uint32_t(min(staged_feature(row), a.n_feat - 1)) * uint32_t(hb) + c;
   }
 #pragma unroll
-  for (int i = 0; i < NX; ++i) {
-    const int row = rx0 + 8 * i + (lane >> 3);
+  for (int i = 0; i < 2; ++i) {
+    const int row = 16 * wave + 8 * i + (lane >> 3);
     int c = ((lane & 7) ^ row_swz(row)) * 16;
     if (a.hidden < kStep) c &= ~64;
     offx[i] = uint32_t(min(row, a.T - 1)) * uint32_t(hb) + c;
   }
-  auto plane_of = [&](int s) { return KSPLIT ? 2 * s + gr : s; };
-  // byte offset in a row of step s (past the last plane: that plane again, which nothing reads)
-  auto step_off = [&](int s) __attribute__((always_inline)) -> int64_t {
-    const int p = min(plane_of(s), planes - 1);
-    return int64_t(p) * kRow - ((half_last && p == planes - 1 && p > 0) ? kRow / 2 : 0);
-  };
-  auto issue_w = [&](int s, uint32_t dst) __attribute__((always_inline)) {
-    const uint8_t* base = wb + step_off(s);
+  auto issue = [&](int s, uint32_t dst) __attribute__((always_inline)) {
+    const int64_t o = plane_offset(s, nk, half_last);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) copy16_to_lds(base, offw[i], dst + (rw0 + 8 * i) * kRow);
-  };
-  auto issue_x = [&](int s, uint32_t dst) __attribute__((always_inline)) {
-    const uint8_t* base = xb + step_off(s);
+    for (int i = 0; i < 4; ++i) copy16_to_lds(wb + o, offw[i], dst + (32 * wave + 8 * i) * kRow);
 #pragma unroll
-    for (int i = 0; i < NX; ++i) copy16_to_lds(base, offx[i], dst + (rx0 + 8 * i) * kRow);
+    for (int i = 0; i < 2; ++i) copy16_to_lds(xb + o, offx[i], dst + W_BYTES + (16 * wave + 8 * i) * kRow);
   };
 
   // ---- operand rows of this wave
   constexpr int kWavesPerHead = D / 64;
-  const int wf = KSPLIT ? (w4 & 1) : w4;
-  const int head_l = wf / kWavesPerHead;
-  const int j0 = (wf % kWavesPerHead) * 32;
+  const int head_l = w4 / kWavesPerHead;
+  const int j0 = (w4 % kWavesPerHead) * 32;
   const int arow0 = head_l * D + j0;
-  const int brow = 64 * (KSPLIT ? (w4 >> 1) : gr);
+  const int brow = 64 * gr;
   const int l16 = lane & 15;
   const int g4 = lane >> 4;
   const int so[2] = {l16 * kRow + ((g4 ^ row_swz(l16)) << 4), l16 * kRow + (((4 + g4) ^ row_swz(l16)) << 4)};
@@ -590,35 +576,19 @@ void qkv_tile_kernel(const QkvArgs a) {
 #pragma unroll
     for (int tb = 0; tb < 4; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Ring positions of the W and x rows of a step. KSPLIT: slots 2 s % 5 and
-  // (2 s + 1) % 5 of the group's ring, walked by `slot`; else stage s % 3.
-  // Group 0 reads step s in interval 2 s, group 1 in 2 s + 1:
-  //  - KSPLIT (a group's ring is its own): W of step s + 2 goes into the slot of
-  //    x of step s - 1 when the group reads step s; x of step s + 2 into the
-  //    slot of W of step s once the barrier after that reading is passed. A
-  //    wave's copies of step s + 1 have landed at the end of its products.
-  //  - else: step s + 2 goes into the stage of step s - 1, last read (by group
-  //    1) in interval 2 s - 1, when a group reads step s; a wave's copies of
-  //    step s + 1 have landed at the end of interval 2 s + 1.
-  const int ring0 = KSPLIT ? gr * G::RING : 0;
-  int slot = 0;
-  auto adv = [](int v, int d) { return v + d >= 5 ? v + d - 5 : v + d; };
-  auto w_pos = [&](int s, int sl) { return KSPLIT ? ring0 + sl * G::W_BYTES : (s % 3) * (G::W_BYTES + G::X_BYTES); };
-  auto x_pos = [&](int s, int sl) {
-    return KSPLIT ? ring0 + adv(sl, 1) * G::W_BYTES : (s % 3) * (G::W_BYTES + G::X_BYTES) + G::W_BYTES;
-  };
-  constexpr int kFly = 4 + NX;   // copies of one step
-  issue_w(0, lds0 + w_pos(0, 0));
-  issue_x(0, lds0 + x_pos(0, 0));
-  issue_w(1, lds0 + w_pos(1, 2));
-  issue_x(1, lds0 + x_pos(1, 2));
+  // Step s is in stage s % 3. Group 0 reads it in interval 2 s, group 1 in 2 s + 1:
+  // step s + 2 goes into the stage of step s - 1, last read (by group 1) in
+  // interval 2 s - 1, when a group reads step s; a wave's copies of step s + 1
+  // have landed at the end of interval 2 s + 1.
+  constexpr int kFly = 6;   // copies of one step
+  issue(0, lds0);
+  issue(1, lds0 + STAGE);
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
   interval_barrier();
   if (gr == 1) interval_barrier();
   int stage = 0;
   for (int s = 0; s < nk; ++s) {
-    const int wst = KSPLIT ? w_pos(s, slot) : stage * (G::W_BYTES + G::X_BYTES);
-    const int xst = KSPLIT ? x_pos(s, slot) : wst + G::W_BYTES;
+    const int wst = stage * STAGE, xst = wst + W_BYTES;
     bf16x8 af[2][4], bx[2][4];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
@@ -628,24 +598,16 @@ void qkv_tile_kernel(const QkvArgs a) {
 #pragma unroll
       for (int tb = 0; tb < 4; ++tb) bx[ks][tb] = ld(xst + (brow + 16 * tb) * kRow + so[ks]);
     }
-    if constexpr (KSPLIT) {
-      issue_w(s + 2, lds0 + ring0 + adv(slot, 4) * G::W_BYTES);
-    } else {
-      const uint32_t nst = (stage == 0 ? 2 : stage - 1) * (G::W_BYTES + G::X_BYTES);
-      issue_w(s + 2, lds0 + nst);
-      issue_x(s + 2, lds0 + nst + G::W_BYTES);
-    }
+    issue(s + 2, lds0 + (stage == 0 ? 2 : stage - 1) * STAGE);
     __builtin_amdgcn_sched_barrier(0);
-    if (!KSPLIT && gr == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
+    if (gr == 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
     interval_barrier();
-    if constexpr (KSPLIT) issue_x(s + 2, lds0 + ring0 + slot * G::W_BYTES);
     __builtin_amdgcn_s_setprio(1);
-    const int p = plane_of(s);
-    const bool half = half_last && p == planes - 1;
+    const bool half = half_last && s == nk - 1;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
-      if (p < planes && !(half && ks == 0)) {
+      if (!(half && ks == 0)) {
 #pragma unroll
         for (int tb = 0; tb < 4; ++tb)
 #pragma unroll
@@ -654,70 +616,197 @@ void qkv_tile_kernel(const QkvArgs a) {
       }
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
-    if (KSPLIT || gr == 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
+    if (gr == 0) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kFly));
     interval_barrier();
-    slot = adv(slot, 2);
     stage = stage == 2 ? 0 : stage + 1;
   }
   if (gr == 0) interval_barrier();
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
   interval_barrier();   // every wave's copies have landed: the ring is free
-
   const int hf = f0 / D + head_l;
-  const bool mine = hf * D >= f_own;
-  if constexpr (KSPLIT) {
-    // Group 0 keeps token blocks 0 and 1, group 1 blocks 2 and 3; the other two
-    // go to the other group's wave of the same features and tokens.
-    f32x4 sum[4][2];
+  if (hf * D >= f_own) store_results<D, 2, 4>(a, acc, hf, j0, t0 + brow, t_own, lds + wave * 4096, lane);
+}
+
+// ---------------------------------------------------------------------------
+// 128 features x 128 tokens. Waves 0-3 multiply (64 features and 64 tokens each,
+// the operand reads of a k-step under the products of the one before), waves 4-7,
+// one on each SIMD beside them, copy; at the end they finish half of the tokens.
+// (Eight multiplying waves of 64 x 32 would read half as much again from LDS,
+// which bounds the kernel: 96 KB a step read and written at 128 bytes a cycle, 768
+// cycles, against 512 of products. 6,144 features, hidden 4,096, T = 576: 32.6
+// us. With the wave groups on alternate steps and their sums added at the end,
+// another order of the sums than the other tiles', it took 33.9.)
+// A ring of five stages of 32 KB, W rows then x rows. At the barrier that starts
+// step s the planes up to s + 1 have landed; step s reads the second k-step of
+// plane s and the first of plane s + 1. The copies that go out after it (plane
+// s + 4) replace plane s - 1, whose last reads fed products before that barrier.
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void qkv_block_kernel(const QkvArgs a) {
+  constexpr int TF = 128, TT = 128, W_BYTES = TF * kRow, STAGE = W_BYTES + TT * kRow, ST = 5;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[ST * STAGE];
+  static_assert(ST * STAGE <= 160 * 1024, "LDS of one CU");
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  const int tile = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+  if (tile >= a.n_ftiles * a.n_ttiles) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w4 = wave & 3;
+  const bool copier = wave >= 4;
+
+  int f_own, t_own;
+  tile_origin(a, tile, TF, TT, f_own, t_own);
+  // (a tile past the last row of W or x is moved back, as above)
+  const int f0 = min(f_own, max(a.n_feat - TF, 0)), t0 = min(t_own, max(a.T - TT, 0));
+  const int nk = (a.hidden + kStep - 1) / kStep;
+  const bool half_last = (a.hidden % kStep) != 0;
+
+  constexpr int kWavesPerHead = D / 64;
+  const int wf = w4 & 1;
+  const int head_l = wf / kWavesPerHead;
+  const int j0 = (wf % kWavesPerHead) * 32;
+  const int brow = 64 * (w4 >> 1);
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int fa = 0; fa < 4; ++fa)
+#pragma unroll
+    for (int tb = 0; tb < 4; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  if (copier) {
+    const int64_t hb = int64_t(a.hidden) * 2;
+    const uint8_t* const wb = a.w + int64_t(f0) * hb;
+    const uint8_t* const xb = a.x + int64_t(t0) * hb;
+    uint32_t offw[4], offx[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 32 * w4 + 8 * i + (lane >> 3);
+      int c = ((lane & 7) ^ row_swz(row)) * 16;
+      if (a.hidden < kStep) c &= ~64;
+      offw[i] = uint32_t(min(staged_feature(row), a.n_feat - 1)) * uint32_t(hb) + c;
+      offx[i] = uint32_t(min(row, a.T - 1)) * uint32_t(hb) + c;
+    }
+    auto issue = [&](int s, int stage) __attribute__((always_inline)) {
+      const int64_t o = plane_offset(s, nk, half_last);
+      const uint32_t dst = lds0 + stage * STAGE + 32 * w4 * kRow;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) copy16_to_lds(wb + o, offw[i], dst + 8 * i * kRow);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) copy16_to_lds(xb + o, offx[i], dst + W_BYTES + 8 * i * kRow);
+    };
+#pragma unroll
+    for (int i = 0; i < ST - 1; ++i) issue(i, i);
+    int stage = ST - 1;
+    for (int s = 0; s < nk; ++s) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(16));   // all but the planes s + 2 and s + 3
+      interval_barrier();
+      issue(s + ST - 1, stage);
+      stage = stage == ST - 1 ? 0 : stage + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  } else {
+    const int arow0 = head_l * D + j0;
+    const int l16 = lane & 15;
+    const int g4 = lane >> 4;
+    const int so[2] = {l16 * kRow + ((g4 ^ row_swz(l16)) << 4), l16 * kRow + (((4 + g4) ^ row_swz(l16)) << 4)};
+    // operand i of a k-step: feature blocks 0 .. 3, then token blocks 0 .. 3
+    bf16x8 op[2][8];
+    auto read = [&](int st, int ks, int i) __attribute__((always_inline)) {
+      const int row = i < 4 ? arow0 + (i >> 1) * (D / 2) + (i & 1) * 16 : TF + brow + 16 * (i - 4);
+      op[ks][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + st + row * kRow + so[ks]));
+    };
+    // The products of k-step ks, with the reads of the k-step after it (the other
+    // register set; stage `st`) between them: two products, one read.
+    auto products = [&](int ks, int st) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int n = 2 * i + u, tb = n >> 2, fa = n & 3;
+          acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[ks][fa], op[ks][4 + tb], acc[fa][tb], 0, 0, 0);
+        }
+        read(st, ks ^ 1, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    int stage = 0;
+    for (int s = 0; s < nk; ++s) {
+      interval_barrier();
+      const int next = stage == ST - 1 ? 0 : stage + 1;
+      if (s == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) read(0, 0, i);
+      }
+      if (half_last && s == nk - 1) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) read(stage * STAGE, 1, i);
+      } else {
+        products(0, stage * STAGE);
+      }
+      products(1, next * STAGE);
+      stage = next;
+    }
+  }
+  interval_barrier();   // every wave's copies have landed: the ring is free
+  // waves 4-7 finish token blocks 2 and 3 of the waves beside them
+  f32x4 fin[4][2];
+  if (!copier) {
 #pragma unroll
     for (int fa = 0; fa < 4; ++fa)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const f32x4 give = gr ? acc[fa][i] : acc[fa][2 + i];
-        sum[fa][i] = gr ? acc[fa][2 + i] : acc[fa][i];
-        *reinterpret_cast<f32x4*>(lds + wave * 8192 + (fa * 2 + i) * 1024 + lane * 16) = give;
+        *reinterpret_cast<f32x4*>(lds + w4 * 8192 + (fa * 2 + i) * 1024 + lane * 16) = acc[fa][2 + i];
+        fin[fa][i] = acc[fa][i];
       }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
-    interval_barrier();
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
+  interval_barrier();
+  if (copier) {
 #pragma unroll
     for (int fa = 0; fa < 4; ++fa)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        sum[fa][i] += *reinterpret_cast<const f32x4*>(lds + (wave ^ 4) * 8192 + (fa * 2 + i) * 1024 + lane * 16);
-    if (mine)
-      store_results<D, 2, 2>(a, sum, hf, j0, t0 + brow + 32 * gr, t_own, lds + G::EXCHANGE + wave * 4096, lane);
-  } else {
-    if (mine) store_results<D, 2, 4>(a, acc, hf, j0, t0 + brow, t_own, lds + wave * 4096, lane);
+        fin[fa][i] = *reinterpret_cast<const f32x4*>(lds + w4 * 8192 + (fa * 2 + i) * 1024 + lane * 16);
   }
+  const int hf = f0 / D + head_l;
+  if (hf * D >= f_own)
+    store_results<D, 2, 2>(a, fin, hf, j0, t0 + brow + (copier ? 32 : 0), t_own, lds + 4 * 8192 + wave * 4096, lane);
 }
 
 // ---------------------------------------------------------------------------
 // Fewest tokens: a workgroup takes 16 FH rotary pairs (2 x 16 FH rows of W) and
 // 16 TB tokens and streams its rows through a ring of ST stages of PL planes
-// (64 hidden each). The waves split a stage by k-step (KW = 2 PL) and, where
-// that leaves waves over, by token blocks; their sums are added at the end.
+// (64 hidden each). All eight waves copy; WF x WT of them multiply, each its
+// share of the 2 FH feature and TB token blocks over all k-steps in order.
 // Bound by the read of W: the ring keeps ST - 1 stages (up to 128 KB) in flight
 // per CU, and the products hide under it.
 // ---------------------------------------------------------------------------
-template <int FH, int TB, int PL, int ST>
+// f(R), f(R - 1), .. f(0), the argument a compile-time constant.
+template <int R, class F>
+__device__ __forceinline__ void countdown(F&& f) {
+  f(std::integral_constant<int, R>{});
+  if constexpr (R > 0) countdown<R - 1>(f);
+}
+
+template <int FH, int TB, int PL, int ST, int WF, int WT>
 struct StreamGeom {
   static constexpr int TF = 32 * FH, TT = 16 * TB, ROWS = TF + TT;
-  static constexpr int KW = 2 * PL, TW = 8 / KW, NB = TB / TW;   // waves over k-steps and tokens; blocks per wave
+  static constexpr int FB = 2 * FH, FW = FB / WF, NB = TB / WT;   // feature blocks; feature and token blocks per wave
   static constexpr int PLANE = ROWS * kRow, STAGE = PL * PLANE;
   static constexpr int COPIES = STAGE / 1024, NC = COPIES / 8;   // 8-row copies per stage, per wave
-  static constexpr int FB = 2 * FH;
-  static constexpr int SUMS = 8 * FB * NB * 1024;
+  static constexpr int SUMS = TB * FB * 1024;
   static constexpr int TAIL = SUMS + TB * FH * 2048;   // sums and cos/sin rows, after the ring is done
   static constexpr int LDS = ST * STAGE > TAIL ? ST * STAGE : TAIL;
-  static_assert(COPIES % 8 == 0 && TW * NB == TB, "even shares");
+  static_assert(COPIES % 8 == 0 && WF * FW == FB && WT * NB == TB && WF * WT <= 8, "even shares");
   static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
 
-template <int D, int FH, int TB, int PL, int ST>
+template <int D, int FH, int TB, int PL, int ST, int WF, int WT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void qkv_stream_kernel(const QkvArgs a) {
-  using G = StreamGeom<FH, TB, PL, ST>;
-  constexpr int FB = G::FB, NB = G::NB, NC = G::NC;
+  using G = StreamGeom<FH, TB, PL, ST, WF, WT>;
+  constexpr int FB = G::FB, FW = G::FW, NB = G::NB, NC = G::NC;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   const int tile = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
@@ -759,36 +848,45 @@ void qkv_stream_kernel(const QkvArgs a) {
   }
   auto issue = [&](int s, int stage) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      // (past the last plane: that plane again, which nothing uses)
-      const int p = min(PL * s + pl[i], planes - 1);
-      const int64_t o = int64_t(p) * kRow - ((half_last && p == planes - 1 && p > 0) ? kRow / 2 : 0);
-      copy16_to_lds(base[i] + o, off[i], lds0 + stage * G::STAGE + (wave + 8 * i) * 1024);
-    }
+    for (int i = 0; i < NC; ++i)
+      copy16_to_lds(base[i] + plane_offset(PL * s + pl[i], planes, half_last), off[i],
+                    lds0 + stage * G::STAGE + (wave + 8 * i) * 1024);
   };
 
-  const int u = wave % G::KW, tw = wave / G::KW;   // this wave's k-step of a stage and token share
-  const int so = l16 * kRow + ((((u & 1) * 4 + g4) ^ row_swz(l16)) << 4) + (u >> 1) * G::PLANE;
-  f32x4 acc[FB][NB];
+  const int wf = wave % WF, wt = wave / WF;   // (a wave with wt >= WT only copies)
+  const int so[2] = {l16 * kRow + ((g4 ^ row_swz(l16)) << 4), l16 * kRow + (((4 + g4) ^ row_swz(l16)) << 4)};
+  const int arow = 16 * FW * wf, brow = G::TF + 16 * NB * wt;
+  f32x4 acc[FW][NB];
 #pragma unroll
-  for (int fa = 0; fa < FB; ++fa)
+  for (int fa = 0; fa < FW; ++fa)
 #pragma unroll
     for (int tb = 0; tb < NB; ++tb) acc[fa][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto compute = [&](int s, int stage) __attribute__((always_inline)) {
-    const int p = PL * s + (u >> 1);
-    if (p >= planes || (half_last && p == planes - 1 && (u & 1) == 0)) return;
-    const uint8_t* st = lds + stage * G::STAGE + so;
-    bf16x8 af[FB], bx[NB];
+    if (wt >= WT) return;
+    const uint8_t* st = lds + stage * G::STAGE;
+    // k-steps of the stage: those of missing planes, and the first of a plane
+    // that holds 32 hidden, are read and not multiplied
+    const int first_half = half_last && (planes - 1) / PL == s ? (planes - 1) % PL : PL;
+    const int np = min(planes - PL * s, PL);
+    bf16x8 af[2 * PL][FW], bx[2 * PL][NB];
 #pragma unroll
-    for (int fa = 0; fa < FB; ++fa) af[fa] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + 16 * fa * kRow));
+    for (int u = 0; u < 2 * PL; ++u) {
+      const uint8_t* p = st + (u >> 1) * G::PLANE + so[u & 1];
 #pragma unroll
-    for (int tb = 0; tb < NB; ++tb)
-      bx[tb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + (G::TF + (tw * NB + tb) * 16) * kRow));
+      for (int fa = 0; fa < FW; ++fa) af[u][fa] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p + (arow + 16 * fa) * kRow));
 #pragma unroll
-    for (int fa = 0; fa < FB; ++fa)
+      for (int tb = 0; tb < NB; ++tb) bx[u][tb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p + (brow + 16 * tb) * kRow));
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int tb = 0; tb < NB; ++tb)
-        acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[fa], bx[tb], acc[fa][tb], 0, 0, 0);
+    for (int u = 0; u < 2 * PL; ++u)
+      if ((u >> 1) < np && !((u & 1) == 0 && (u >> 1) == first_half)) {
+#pragma unroll
+        for (int fa = 0; fa < FW; ++fa)
+#pragma unroll
+          for (int tb = 0; tb < NB; ++tb)
+            acc[fa][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[u][fa], bx[u][tb], acc[fa][tb], 0, 0, 0);
+      }
   };
   // Stage s % ST holds step s. At the barrier of step s every wave's copies of
   // step s have landed (ST - 2 younger steps stay in flight) and every wave's
@@ -804,32 +902,31 @@ void qkv_stream_kernel(const QkvArgs a) {
     compute(s, stage);
     stage = stage == ST - 1 ? 0 : stage + 1;
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-  interval_barrier();
-  for (; s < nk; ++s) {   // the last steps are all there
+  countdown<ST - 2>([&](auto younger) __attribute__((always_inline)) {   // the last steps
+    constexpr int R = decltype(younger)::value;
+    if (nk - 1 - s != R) return;
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(NC * R));
+    interval_barrier();
     compute(s, stage);
     stage = stage == ST - 1 ? 0 : stage + 1;
-  }
+    ++s;
+  });
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
   interval_barrier();   // every wave is done with the ring
-  // ---- add the waves' sums: wave tb finishes token block tb
+  // ---- wave tb finishes token block tb: its sums from the waves that hold them
+  if (wt < WT) {
 #pragma unroll
-  for (int fa = 0; fa < FB; ++fa)
+    for (int fa = 0; fa < FW; ++fa)
 #pragma unroll
-    for (int tb = 0; tb < NB; ++tb)
-      *reinterpret_cast<f32x4*>(lds + ((wave * NB + tb) * FB + fa) * 1024 + lane * 16) = acc[fa][tb];
+      for (int tb = 0; tb < NB; ++tb)
+        *reinterpret_cast<f32x4*>(lds + ((wt * NB + tb) * FB + wf * FW + fa) * 1024 + lane * 16) = acc[fa][tb];
+  }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
   interval_barrier();
   if (wave >= TB) return;
   f32x4 sum[FB][1];
 #pragma unroll
-  for (int fa = 0; fa < FB; ++fa) {
-    sum[fa][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int v = 0; v < G::KW; ++v)
-      sum[fa][0] += *reinterpret_cast<const f32x4*>(
-          lds + ((((wave / NB) * G::KW + v) * NB + wave % NB) * FB + fa) * 1024 + lane * 16);
-  }
+  for (int fa = 0; fa < FB; ++fa) sum[fa][0] = *reinterpret_cast<const f32x4*>(lds + (wave * FB + fa) * 1024 + lane * 16);
   const int tfirst = t0 + 16 * wave;
   store_results<D, FH, 1>(a, sum, hf, j0, tfirst, tfirst, lds + G::SUMS + wave * FH * 2048, lane);
 }
@@ -841,17 +938,18 @@ cw_status check_launch(const char* what) {
 }
 
 // The tile shapes, and what a call costs with each: `tiles` tiles in rounds of
-// one per CU, a round fixed + planes * us (planes = hidden / 64), where us grows
+// one per CU, a round fixed + planes * us (planes = hidden / 64), where us goes
 // from `light` (few CUs busy) to `full` (all busy). The shape with the smallest
-// estimate is taken. The constants are fits to calls measured back to back at
-// T = 1 .. 8,000 tokens, 384 .. 10,240 features and hidden 256 .. 8,192 (all
-// shapes at each size): the estimate's choice is within 3.2 % of the best shape
-// everywhere and 0.1 % on average. Leaving out any one shape costs 17 to 59 %
-// at its sizes (the 32 x 16 tile: 17 %). Examples, in us, 6,144 features and
-// hidden 4,096, 256 x 256 tile against the chosen one: T = 16: 66.4 / 10.9
-// (32 x 16); 64: 67.3 / 15.3 (32 x 64); 128: 68.3 / 20.0 (64 x 64); 256: 70.8 /
-// 27.0 (64 x 128); 576: 71.6 / 33.9 (128 x 128); 1,024: 72.3 / 52.0 (256 x 128);
-// 1,536: 75.8 (128 x 128: 93.3).
+// estimate is taken; all give the same bits. The constants are fits to calls in
+// captured graphs at 180 sizes: T = 1 .. 8,000 tokens, 384 .. 10,240 features,
+// hidden 256 .. 8,192, all shapes at each (profiles/qkv_tile_shapes.txt). The
+// estimate's choice is within 2.6 % of the best shape everywhere and 0.05 % on
+// average. Leaving out any one shape costs 13 % (256 x 256) to 63 % (128 x 128)
+// at its sizes; a 64 x 128 tile was the best by more than 1 % at two of the 180
+// (by 4 and 9 %, 0.3 and 0.6 us) and is left out. Examples, in us, 6,144 features
+// and hidden 4,096, 256 x 256 tile against the chosen one: T = 64: 67.2 / 16.7
+// (32 x 64); 128: 68.3 / 20.9 (64 x 64); 256: 70.4 / 27.2 (128 x 128); 576: 72.1
+// / 32.6 (128 x 128); 1,024: 72.6 / 50.8 (256 x 128); 1,536: 77.0 (128 x 128: 85.5).
 struct QkvShape {
   int tile_f, tile_t;
   bool persistent;
@@ -860,14 +958,13 @@ struct QkvShape {
   void (*kernel64)(QkvArgs);
 };
 const QkvShape kShapes[] = {
-    {256, 256, true, 8.7, 0.90, 1.38, qkv_rope_append_kernel<128>, qkv_rope_append_kernel<64>},
-    {256, 128, false, 5.5, 0.565, 0.83, qkv_tile_kernel<128, false>, qkv_tile_kernel<64, false>},
-    {128, 128, false, 5.0, 0.325, 0.46, qkv_tile_kernel<128, true>, qkv_tile_kernel<64, true>},
-    {64, 128, false, 4.4, 0.34, 0.38, qkv_stream_kernel<128, 2, 8, 2, 3>, qkv_stream_kernel<64, 2, 8, 2, 3>},
-    {64, 64, false, 3.7, 0.242, 0.27, qkv_stream_kernel<128, 2, 4, 2, 5>, qkv_stream_kernel<64, 2, 4, 2, 5>},
-    {32, 64, false, 3.7, 0.173, 0.21, qkv_stream_kernel<128, 1, 4, 2, 6>, qkv_stream_kernel<64, 1, 4, 2, 6>},
-    {32, 32, false, 3.9, 0.104, 0.14, qkv_stream_kernel<128, 1, 2, 4, 5>, qkv_stream_kernel<64, 1, 2, 4, 5>},
-    {32, 16, false, 3.7, 0.100, 0.13, qkv_stream_kernel<128, 1, 1, 4, 6>, qkv_stream_kernel<64, 1, 1, 4, 6>},
+    {256, 256, true, 13.4, 0.768, 1.297, qkv_rope_append_kernel<128>, qkv_rope_append_kernel<64>},
+    {256, 128, false, 6.97, 0.529, 0.754, qkv_tile_kernel<128>, qkv_tile_kernel<64>},
+    {128, 128, false, 5.52, 0.296, 0.400, qkv_block_kernel<128>, qkv_block_kernel<64>},
+    {64, 64, false, 4.11, 0.255, 0.242, qkv_stream_kernel<128, 2, 4, 2, 5, 2, 2>, qkv_stream_kernel<64, 2, 4, 2, 5, 2, 2>},
+    {32, 64, false, 3.88, 0.187, 0.182, qkv_stream_kernel<128, 1, 4, 2, 6, 2, 2>, qkv_stream_kernel<64, 1, 4, 2, 6, 2, 2>},
+    {32, 32, false, 3.45, 0.129, 0.122, qkv_stream_kernel<128, 1, 2, 4, 5, 2, 2>, qkv_stream_kernel<64, 1, 2, 4, 5, 2, 2>},
+    {32, 16, false, 3.52, 0.100, 0.092, qkv_stream_kernel<128, 1, 1, 4, 6, 2, 1>, qkv_stream_kernel<64, 1, 1, 4, 6, 2, 1>},
 };
 
 const QkvShape& pick_shape(int64_t rows, int64_t n_feat, int64_t hidden) {

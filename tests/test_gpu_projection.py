@@ -21,6 +21,7 @@ import math
 
 import numpy as np
 import pytest
+import test_gpu_parity as GP
 import torch
 
 from oracle import paged as OP
@@ -238,31 +239,77 @@ def test_llama70b_long_sampled():
 
 
 
-TILES = [
-    # (tile features x tokens the size selects) edges of tiles, odd and half steps of hidden, several rounds
-    ("32x16-one", 1, 1, 128, 96, [0], [1], {}),
-    ("32x16-two", 8, 2, 128, 1056, [16, 0], [9, 8], {"bias": False}),
-    ("32x16-d64", 2, 1, 64, 672, [0, 48], [15, 1], {}),
-    ("32x32", 28, 4, 128, 160, [0], [31], {}),
-    ("32x64", 28, 4, 128, 2080, [32], [33], {}),
-    ("32x64-d64", 28, 4, 64, 160, [0, 16, 0], [30, 0, 35], {"bias": False}),
-    ("64x64", 28, 4, 128, 1056, [0, 0], [64, 65], {}),
-    ("64x64-d64", 28, 4, 64, 1056, [16], [200], {}),
-    ("64x128", 28, 4, 128, 1056, [0, 48], [129, 171], {}),
-    ("64x128-d64", 28, 4, 64, 2080, [0], [500], {"bias": False}),
-    ("128x128", 28, 4, 128, 2080, [0, 16], [257, 190], {}),
-    ("128x128-d64", 28, 4, 64, 544, [0], [1100], {}),
-    ("256x128", 28, 4, 128, 544, [0, 32, 0], [700, 1, 499], {}),
-    ("256x128-rounds", 28, 4, 64, 1056, [0], [2100], {"bias": False}),
-    ("256x256", 28, 4, 128, 1056, [0, 0], [1025, 1075], {}),
-    # more tiles than workgroups: the ring runs on across tiles
-    ("256x256-rounds", 64, 16, 64, 544, [0, 16, 0, 0], [2500, 0, 1999, 2], {}),
-]
+# Kernel of each tile shape (features x tokens), and row counts that select it with
+# 25 / 5 heads of 128 (4,480 features) and 27 / 3 of 64 (2,112): neither a multiple
+# of 256. The row counts are edges of the tile's range and of tiles of tokens.
+TILES = {
+    "32x16": ("qkv_stream_kernel<{D}, 1, 1, 4, 6, 2, 1>", {128: [1, 15, 16], 64: [1, 17, 47]}),
+    "32x32": ("qkv_stream_kernel<{D}, 1, 2, 4, 5, 2, 2>", {128: [17, 31, 32], 64: [63, 65, 96]}),
+    "32x64": ("qkv_stream_kernel<{D}, 1, 4, 2, 6, 2, 2>", {128: [33, 63, 64], 64: [97, 127, 129]}),
+    "64x64": ("qkv_stream_kernel<{D}, 2, 4, 2, 5, 2, 2>", {128: [65, 127, 129], 64: [193, 255, 257]}),
+    "128x128": ("qkv_block_kernel<{D}>", {128: [193, 257, 511], 64: [449, 513, 897]}),
+    "256x128": ("qkv_tile_kernel<{D}>", {128: [897, 1023, 1025], 64: [1921, 2049]}),
+    "256x256": ("qkv_rope_append_kernel<{D}>", {128: [1793, 2049], 64: [3841, 4097]}),
+}
+HEADS = {128: (25, 5), 64: (27, 3)}
 
 
-@pytest.mark.parametrize("name,hq,hkv,D,hidden,plen,slen,kw", TILES, ids=[c[0] for c in TILES])
-def test_tile_edges_and_rounds(name, hq, hkv, D, hidden, plen, slen, kw):
-    _ragged(name, hq, hkv, D, hidden, plen, slen, seed=21, **kw).run().check_full()
+def _tile_of(names):
+    """Tile shape and head_dim of the projection kernel among `names`."""
+    return [(tile, D) for tile, (kernel, rows) in TILES.items() for D in rows
+            if any(kernel.format(D=D) in n for n in names)]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("tile", TILES)
+def test_every_tile_shape(tile, D):
+    """Each shape at the edges of its tiles, with one to 17 steps of hidden, whole
+    and half (hidden below 160 never takes the 32 x 16 tile)."""
+    kernel, rows = TILES[tile]
+    for n, T in enumerate(rows[D]):
+        for hidden in [160, 672, 1056] if tile == "32x16" else [32, 64, 96, 160, 1056]:
+            cut = T // 3
+            slen, plen = ([cut, 0, T - cut], [16, 48, 0]) if cut else ([T], [32])
+            c = _ragged(f"{tile} T={T} hidden={hidden} D={D}", *HEADS[D], D, hidden, plen, slen, seed=21,
+                        bias=n % 2 == 0)
+            assert _tile_of(GP.kernels(c.run)) == [(tile, D)], c.name
+            c.check_full() if T * hidden < 1e6 else c.check_sampled()
+
+
+@pytest.mark.parametrize("hidden", [32, 96, 192])
+@pytest.mark.parametrize("D", [64, 128])
+def test_persistent_ring_runs_on_across_tiles(hidden, D):
+    """More tiles than workgroups (1.75 rounds) at one, two and three steps a tile:
+    a tile's first copies go out during the tile before it."""
+    hq, hkv = (128, 64) if D == 64 else (64, 32)
+    c = _ragged(f"rounds-h{hidden}-d{D}", hq, hkv, D, hidden, [0, 16, 0, 0], [900, 0, 699, 2], seed=22)
+    assert _tile_of(GP.kernels(c.run)) == [("256x256", D)]
+    c.check_sampled(n_random=400)
+
+
+@pytest.mark.parametrize("hidden", [96, 1056])
+@pytest.mark.parametrize("D", [64, 128])
+def test_rows_alone_equal_rows_in_a_batch(D, hidden):
+    """A request projected by itself gives the bits that it gets in a batch, with
+    every tile shape (each sums over hidden in the same order)."""
+    hq, hkv = HEADS[D]
+    slen = [1, 17, 40, 70, 100, 200, 300, 480, 950, 2200] if D == 64 else [1, 17, 40, 70, 200, 300, 480, 950]
+    plen = [16 * (i % 4) for i in range(len(slen))]
+    c = _ragged(f"batch of {len(slen)}", hq, hkv, D, hidden, plen, slen, seed=25)
+    seen = set(_tile_of(GP.kernels(c.run)))
+    for r, (n, P) in enumerate(zip(slen, plen)):
+        c0 = int(c.cu[r])
+        one = _ragged(f"request of {n}", hq, hkv, D, hidden, [P], [n], seed=25)
+        one.x, one.w, one.b = c.x[c0:c0 + n], c.w, c.b
+        seen |= set(_tile_of(GP.kernels(one.run)))
+        assert np.array_equal(_bits(one.q), _bits(c.q[c0:c0 + n])), (one.name, "q")
+        for name in ("kc", "vc"):
+            got, all_ = _bits(getattr(one, name)), _bits(getattr(c, name))
+            pos = P + np.arange(n)
+            rows = got[one.bt[0][pos // BS], :, pos % BS]
+            assert np.array_equal(rows, all_[c.bt[r][pos // BS], :, pos % BS]), (one.name, name)
+    # (32 x 16 is not taken at hidden 96)
+    assert seen == {(t, D) for t in TILES if hidden > 96 or t != "32x16"}, seen
 
 
 def _many_requests(total, seed):
