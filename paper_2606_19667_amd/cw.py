@@ -388,8 +388,12 @@ def _dev(t: torch.Tensor, dtype, name: str) -> int:
 
 
 def _stream(stream) -> int:
-    if stream is None:   # the handle of torch.cuda.current_stream(), without the object
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if stream is None:
+        # the handle of torch.cuda.current_stream(), without the object; where torch
+        # has not initialised the GPU (a forked child above all) it raises or does so
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
 

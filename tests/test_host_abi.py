@@ -9,6 +9,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import paged
 from paper_2606_19667_amd import cw, workload as W
@@ -659,3 +660,15 @@ def test_fused_call_validates_its_plan_before_launch():
     assert "cw_suffix_prefill_append_attn" in cw.last_error()
     assert _fused_call([0, 0], [16], bt[:1], cw.suffix_prefill_append_plan([0, 0], [16], bt[:1], 8, 2, 128, 100)) \
         == cw.CW_OK                                                    # nothing to do: no launch
+
+
+def test_default_stream_is_refused_where_torch_refuses_the_gpu(monkeypatch):
+    """The default stream is torch's: where torch has not initialised the GPU it
+    decides, and raises in a child forked from a process that uses one (a launch
+    there would work on the parent's state)."""
+    def refuse():
+        raise RuntimeError("forked subprocess")
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    monkeypatch.setattr(torch.cuda, "current_stream", refuse)
+    with pytest.raises(RuntimeError, match="forked subprocess"):
+        cw._stream(None)
