@@ -238,6 +238,53 @@ def test_llama70b_long_sampled():
     c.run().check_sampled()
 
 
+RAGGED = [
+    # (query heads, KV heads, head_dim, hidden, prefixes, suffixes)
+    (1, 1, 128, 96, [0], [1], {}),
+    (8, 2, 128, 1056, [16, 0], [9, 8], {"bias": False}),
+    (2, 1, 64, 672, [0, 48], [15, 1], {}),
+    (28, 4, 128, 160, [0], [31], {}),
+    (28, 4, 128, 2080, [32], [33], {}),
+    (28, 4, 64, 160, [0, 16, 0], [30, 0, 35], {"bias": False}),
+    (28, 4, 128, 1056, [0, 0], [64, 65], {}),
+    (28, 4, 64, 1056, [16], [200], {}),
+    (28, 4, 128, 1056, [0, 48], [129, 171], {}),
+    (28, 4, 64, 2080, [0], [500], {"bias": False}),
+    (28, 4, 128, 2080, [0, 16], [257, 190], {}),
+    (28, 4, 64, 544, [0], [1100], {}),
+    (28, 4, 128, 544, [0, 32, 0], [700, 1, 499], {}),
+    (28, 4, 64, 1056, [0], [2100], {"bias": False}),
+    (28, 4, 128, 1056, [0, 0], [1025, 1075], {}),
+    (64, 16, 64, 544, [0, 16, 0, 0], [2500, 0, 1999, 2], {}),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,D,hidden,plen,slen,kw", RAGGED,
+                         ids=[f"{c[0]}-{c[1]}-{c[2]}-h{c[3]}-t{sum(c[5])}" for c in RAGGED])
+def test_ragged_heads_and_hidden(hq, hkv, D, hidden, plen, slen, kw):
+    _ragged(f"ragged T={sum(slen)}", hq, hkv, D, hidden, plen, slen, seed=21, **kw).run().check_full()
+
+
+@pytest.mark.parametrize("T", [15, 60, 700, 1300])
+def test_results_at_8_byte_alignment(T):
+    """The epilogue stores 16 bytes at a time; results whose storage starts at 8
+    bytes past a multiple of 16 get the same bits."""
+    c = _ragged(f"8-byte aligned T={T}", 24, 4, 128, 160, [16], [T], seed=26).run()
+    meta = cw.BatchMeta(c.bt, c.cu, c.plen, c.hq, c.hkv, c.D)
+    rope = torch.from_numpy(cw.rope_table(int(c.pos.max()) + 1, c.D, c.base)).cuda()
+
+    def shifted(t):
+        flat = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")
+        view = flat[4:].view(t.shape)
+        view.copy_(t)
+        assert view.data_ptr() % 16 == 8
+        return view
+    q, kc, vc = shifted(torch.zeros_like(c.q)), shifted(c.k0), shifted(c.v0)
+    cw.qkv_rope_append(meta, c.x.cuda(), c.w.cuda(), rope, kc, vc, bias=c.b.cuda(), q_out=q)
+    torch.cuda.synchronize()
+    for got, expect in ((q, c.q), (kc, c.kc), (vc, c.vc)):
+        assert np.array_equal(_bits(got), _bits(expect)), c.name
+
 
 # Kernel of each tile shape (features x tokens), and row counts that select it with
 # 25 / 5 heads of 128 (4,480 features) and 27 / 3 of 64 (2,112): neither a multiple
