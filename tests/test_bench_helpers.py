@@ -40,3 +40,13 @@ def test_more_than_one_gpu_is_refused():
                        text=True, timeout=120)
     assert p.returncode != 0
     assert "one GPU" in (p.stdout + p.stderr) or "1 GPU" in (p.stdout + p.stderr)
+
+
+def test_kernel_name_out_of_a_symbol():
+    args = "((anonymous namespace)::AttnArgs)"
+    assert bench.kernel_name(f"void (anonymous namespace)::suffix_prefill_stream_kernel<true>{args}") == \
+        "suffix_prefill_stream_kernel<true>"
+    assert bench.kernel_name(f"(anonymous namespace)::suffix_prefill_attn_kernel<128, false, true>{args} [clone .kd]") \
+        == "suffix_prefill_attn_kernel<128, false, true>"
+    assert bench.kernel_name("kv_append_kernel(int)") == "kv_append_kernel"
+    assert bench.kernel_name("hipMemcpyAsync") is None
