@@ -379,6 +379,125 @@ struct AttnArgs {
   uint32_t fp_lo, fp_hi; // the batch fingerprint the host validated
 };
 
+// Causal mask of a step's scores: element e of accumulator h holds key
+// 32 h + (e / 8) 16 + e % 8 (the lane half's 8 are in `lim`, so that the
+// per-element terms stay immediates); keys above lim are not visible. Each element
+// is pinned after its select: otherwise the compiler keeps all 32 compare results
+// live as lane masks in scalar registers.
+__device__ __forceinline__ void causal_mask(f32x16 (&sc)[2], int lim) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int e2 = 0; e2 < 16; ++e2) {
+      if (h * 32 + (e2 >> 3) * 16 + (e2 & 7) > lim) sc[h][e2] = -INFINITY;
+      asm volatile("" : "+v"(sc[h][e2]));
+    }
+}
+
+// Maximum of a row over a step's 64 keys (this lane's 32 and lane ^ 32's).
+__device__ __forceinline__ float row_max(const f32x16 (&sc)[2]) {
+  float x = fmaxf(fmaxf(sc[0][0], sc[0][1]), sc[0][2]);
+  float y = fmaxf(fmaxf(sc[1][0], sc[1][1]), sc[1][2]);
+#pragma unroll
+  for (int e2 = 3; e2 < 15; e2 += 2) {
+    x = fmaxf(fmaxf(x, sc[0][e2]), sc[0][e2 + 1]);
+    y = fmaxf(fmaxf(y, sc[1][e2]), sc[1][e2 + 1]);
+  }
+  x = fmaxf(fmaxf(x, sc[0][15]), sc[1][15]);
+  return max_pair32(fmaxf(x, y));
+}
+
+// Per-lane LDS read offsets of the MFMA operands (ring position 0; a position
+// adds its stride).
+template <int D>
+__device__ __forceinline__ void operand_offsets(int lane, int l32, int half, int& k_off, int& v_off0, int& v_off1) {
+  constexpr int RB = AttnGeom<D>::RB, KREG = AttnGeom<D>::KREG;
+  // K operand: key 32 h + pi(l32) (block 2 h + l32 / 16, row pi(l32) % 16),
+  // chunk 2 s + half; in the chunk-major block layout that is the lane's base
+  // plus h 32 RB + s 512.
+  const int k_row = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
+  k_off = (l32 >> 4) * (kBs * RB) + half * 256 + (k_row & 15) * 16;
+  // V operand (transposing reads, two per operand): in each 16-lane group a
+  // lane names 4 values of d of one key, and lane 4 q + s receives value s of
+  // the 4 keys named by lanes q, q + 4, q + 8, q + 12. Lane j of group gq names
+  // key 8 half + 4 rd + j / 4 of the block (rd: first or second read) and
+  // d = 32 t + 16 (gq % 2) + 4 (j % 4), so lane l32 receives row d = 32 t + l32,
+  // keys 8 half + 4 rd .. + 3: with both reads the operand of keys
+  // 8 half .. + 7. In the swizzled chunk-major layout that is the lane's base
+  // (chunk c % 4 = 2 (gq % 2) + (j % 4) / 2) plus t 1024 + kk BLK.
+  const int vj = lane & 15, vpart = 2 * ((lane >> 4) & 1) + ((vj & 3) >> 1);
+  v_off0 = KREG + vpart * 256 + (((8 * half + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
+  v_off1 = KREG + vpart * 256 + (((8 * half + 4 + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
+  // Hide the bases' known bits from the compiler: otherwise it rewrites
+  // base + constant as base | constant, which it cannot fold into the LDS
+  // instructions' offset field, and keeps one register per read instead.
+  asm volatile("" : "+v"(k_off));
+  asm volatile("" : "+v"(v_off0));
+  asm volatile("" : "+v"(v_off1));
+}
+
+// Rounds a wave's output (normalised by `inv`) to bf16 and stores it. Rows of the
+// tile: lanes that read staged row rr hold column m' = 32 wave + rr of the tile,
+// i.e. head head0 + m' / T and position m' % T (T = a.per_tile; the quotient by a
+// multiply with tdiv, exact for m' < 256). `stg`: the wave's staging area. (The
+// arguments come by value: through a reference the compiler moves their loads.)
+template <int D>
+__device__ __forceinline__ void store_output(const AttnArgs a, const f32x16 (&oacc)[D / 32], float inv, uint32_t tdiv,
+                                             uint8_t* stg, int lane, int wave, int qrow0, int nvalid, int head0) {
+  using G = AttnGeom<D>;
+  // A lane holds 4 consecutive d of its row per (t, gq), so direct stores would
+  // write 32 rows in 8-byte pieces per instruction. Each round stages a range of d
+  // (HD values) of all 32 rows and reads it back as rows of 16-byte chunks, so
+  // that each store covers whole 128-byte lines of HD values (16-byte chunk c of
+  // staged row r at position c ^ (r % CPR): conflict-free writes and reads). Lanes
+  // read what other lanes wrote: the hardware keeps a wave's LDS accesses in
+  // order, and empty asm statements with a memory clobber keep the compiler from
+  // reusing, for a lane, values it loaded before another lane's writes (as it may,
+  // for memory it sees no other thread write).
+  constexpr int HD = G::STAGING / (32 * 2);   // d values per round (64)
+  constexpr int CPR = HD / 8;                // 16-byte chunks per staged row
+  constexpr int TPR = HD / 32;               // output tiles per round
+  constexpr int RPI = 64 / CPR;              // staged rows per read instruction
+  static_assert(D % HD == 0 && CPR == 8, "staging rounds");
+  // Opaque copies of the values the addresses below derive from: without
+  // them the compiler computes those (entry- or lane-invariant) addresses
+  // before the steps and keeps them live across the step loop.
+  int ln = lane, q0 = qrow0, nv = nvalid, hg = head0;
+  asm volatile("" : "+v"(ln), "+s"(q0), "+s"(nv), "+s"(hg));
+  const int l32e = ln & 31, halfe = ln >> 5;
+#pragma unroll
+  for (int rd = 0; rd < D / HD; ++rd) {
+#pragma unroll
+    for (int tt = 0; tt < TPR; ++tt)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const int t = rd * TPR + tt, c = tt * 4 + gq;   // d = 32 t + 8 gq + 4 half ..
+        const u32x2 w{pack_bf16x2(oacc[t][gq * 4 + 0] * inv, oacc[t][gq * 4 + 1] * inv),
+                      pack_bf16x2(oacc[t][gq * 4 + 2] * inv, oacc[t][gq * 4 + 3] * inv)};
+        *reinterpret_cast<u32x2*>(stg + l32e * (HD * 2) + ((c ^ (l32e % CPR)) << 4) + halfe * 8) = w;
+      }
+    asm volatile("" ::: "memory");
+    // all of the round's reads first, then the stores of the rows that exist
+    u32x4 v[32 / RPI];
+#pragma unroll
+    for (int q = 0; q < 32 / RPI; ++q) {
+      const int r = q * RPI + ln / CPR, c = ln % CPR;
+      v[q] = *reinterpret_cast<const u32x4*>(stg + r * (HD * 2) + ((c ^ (r % CPR)) << 4));
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < 32 / RPI; ++q) {
+      const int r = q * RPI + ln / CPR, c = ln % CPR;
+      // the staged row's column of the tile, its head and position
+      const uint32_t mr = uint32_t(wave * 32 + r);
+      const int hr = int((mr * tdiv) >> 16);
+      const int pr = int(mr) - hr * a.per_tile;
+      if (hr < a.group && pr < nv)
+        *reinterpret_cast<u32x4*>(a.out + ((int64_t(q0) + pr) * a.hq + hg + hr) * D + rd * HD + c * 8) = v[q];
+    }
+  }
+}
+
 // SPLIT: entries may cover only part of a tile's key range (the planner cuts
 // each tile into num_splits runs of whole steps); an entry then writes, for its
 // rows, the attention over its keys only: O normalised in fp32 to
@@ -712,29 +831,8 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
     asm volatile("" ::: "memory");
   };
 
-  // ---- per-lane LDS read offsets (ring position 0; a position adds its stride)
-  // K operand: key 32 h + pi(l32) (block 2 h + l32 / 16, row pi(l32) % 16),
-  // chunk 2 s + half; in the chunk-major block layout that is the lane's base
-  // plus h 32 RB + s 512.
-  const int k_row = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-  int k_off = (l32 >> 4) * (kBs * RB) + half * 256 + (k_row & 15) * 16;
-  // V operand (transposing reads, two per operand): in each 16-lane group a
-  // lane names 4 values of d of one key, and lane 4 q + s receives value s of
-  // the 4 keys named by lanes q, q + 4, q + 8, q + 12. Lane j of group gq names
-  // key 8 half + 4 rd + j / 4 of the block (rd: first or second read) and
-  // d = 32 t + 16 (gq % 2) + 4 (j % 4), so lane l32 receives row d = 32 t + l32,
-  // keys 8 half + 4 rd .. + 3: with both reads the operand of keys
-  // 8 half .. + 7. In the swizzled chunk-major layout that is the lane's base
-  // (chunk c % 4 = 2 (gq % 2) + (j % 4) / 2) plus t 1024 + kk BLK.
-  const int vj = lane & 15, vpart = 2 * ((lane >> 4) & 1) + ((vj & 3) >> 1);
-  int v_off0 = KREG + vpart * 256 + (((8 * half + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
-  int v_off1 = KREG + vpart * 256 + (((8 * half + 4 + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
-  // Hide the bases' known bits from the compiler: otherwise it rewrites
-  // base + constant as base | constant, which it cannot fold into the LDS
-  // instructions' offset field, and keeps one register per read instead.
-  asm volatile("" : "+v"(k_off));
-  asm volatile("" : "+v"(v_off0));
-  asm volatile("" : "+v"(v_off1));
+  int k_off, v_off0, v_off1;
+  operand_offsets<D>(lane, l32, half, k_off, v_off0, v_off1);
   auto rd16 = [&](int addr) __attribute__((always_inline)) -> bf16x8 {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + addr));
   };
@@ -804,10 +902,7 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
-  // Output rows of the staged read-back (unsplit kernel): the lanes reading
-  // staged row rr hold column m' = 32 wave + rr of the tile, i.e. head m' / T
-  // and position m' % T (T = a.per_tile; the quotient by a multiply, exact for
-  // m' < 256).
+  // Divides a column of the tile (below 256) by a.per_tile (store_output).
   const uint32_t tdiv = (65536u + uint32_t(a.per_tile) - 1) / uint32_t(a.per_tile);
 
   for (int e = blockIdx.x; e < a.num_entries; e += grid) {
@@ -865,33 +960,8 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
         qf[s] = row_ok ? scale_bf16x8(qn[s], a.c_log2) : __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
     }
 
-    // Causal mask of the step starting at key k0: element e of accumulator h
-    // holds key k0 + 32 h + (e / 8) 16 + half 8 + e % 8; the lane term moves to
-    // the limit so that the per-element terms stay immediates.
-    // (each element is pinned after its select: otherwise the compiler keeps
-    // all 32 compare results live as lane masks in scalar registers)
-    auto mask = [&](f32x16 (&sc)[2], int k0) __attribute__((always_inline)) {
-      const int lim = qpos - k0 - half * 8;
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int e2 = 0; e2 < 16; ++e2) {
-          if (h * 32 + (e2 >> 3) * 16 + (e2 & 7) > lim) sc[h][e2] = -INFINITY;
-          asm volatile("" : "+v"(sc[h][e2]));
-        }
-    };
-    // Maximum of the row over a step's 64 keys (this lane's 32 and lane ^ 32's).
-    auto rowmax = [&](const f32x16 (&sc)[2]) __attribute__((always_inline)) -> float {
-      float x = fmaxf(fmaxf(sc[0][0], sc[0][1]), sc[0][2]);
-      float y = fmaxf(fmaxf(sc[1][0], sc[1][1]), sc[1][2]);
-#pragma unroll
-      for (int e2 = 3; e2 < 15; e2 += 2) {
-        x = fmaxf(fmaxf(x, sc[0][e2]), sc[0][e2 + 1]);
-        y = fmaxf(fmaxf(y, sc[1][e2]), sc[1][e2 + 1]);
-      }
-      x = fmaxf(fmaxf(x, sc[0][15]), sc[1][15]);
-      return max_pair32(fmaxf(x, y));
-    };
+    // Causal mask: key k0 + i of the step is visible up to the lane's position.
+    auto mask = [&](f32x16 (&sc)[2], int k0) __attribute__((always_inline)) { causal_mask(sc, qpos - k0 - half * 8); };
 
     float l_run = 0.f;   // this lane's partial row sum (its 32 keys per step)
     const bf16x2 ones{(__bf16)1.0f, (__bf16)1.0f};
@@ -1104,7 +1174,7 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
       // so for the first run: key 0 is visible to every row). A row that sees no
       // key of the run's first step sees none of its later steps either (they
       // hold higher keys), so any base serves it.
-      float m0 = rowmax(sa);
+      float m0 = row_max(sa);
       if (m0 == -INFINITY) m0 = 0.f;
 #pragma unroll
       for (int h = 0; h < 2; ++h) sa[h] -= m0;
@@ -1248,8 +1318,8 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
 
     const float l_tot = sum_pair32(l_run);
     if constexpr (SPLIT) {
-      // Partial output in fp32, through this wave's staging area (as the
-      // unsplit output below): a lane holds 4 consecutive d of its row per
+      // Partial output in fp32, through this wave's staging area (as in
+      // store_output): a lane holds 4 consecutive d of its row per
       // (t, gq), so direct stores would write 32 rows in 32-byte pieces per
       // instruction. Each round stages 32 values of d of all 32 rows (16-byte
       // chunk c of row r at position c ^ (r % 8)) and stores whole 128-byte
@@ -1291,61 +1361,8 @@ void suffix_prefill_attn_kernel(const AttnArgs a) {
       if (row_ok && half == 0)
         a.part_lse[int64_t(split) * a.part_rows + qrow * a.hq + head] = any ? -mneg[0] + __log2f(l_tot) : -INFINITY;
     } else {
-      // The output goes through this wave's staging area: a lane holds 4
-      // consecutive d of its row per (t, gq), so direct stores would write 32
-      // rows in 8-byte pieces per instruction. Each round stages a range of d
-      // (HD values) of all 32 rows and reads it back as rows of 16-byte
-      // chunks, so that each store covers whole 128-byte lines of HD values
-      // (16-byte chunk c of staged row r at position c ^ (r % CPR):
-      // conflict-free writes and reads). Lanes read what other lanes wrote:
-      // the hardware keeps a wave's LDS accesses in order, and empty asm
-      // statements with a memory clobber keep the compiler from reusing, for
-      // a lane, values it loaded before another lane's writes (as it may, for
-      // memory it sees no other thread write).
-      constexpr int HD = G::STAGING / (32 * 2);   // d values per round (64)
-      constexpr int CPR = HD / 8;                // 16-byte chunks per staged row
-      constexpr int TPR = HD / 32;               // output tiles per round
-      constexpr int RPI = 64 / CPR;              // staged rows per read instruction
-      static_assert(D % HD == 0 && CPR == 8, "staging rounds");
       const float inv = row_ok ? __builtin_amdgcn_rcpf(l_tot) : 0.f;
-      uint8_t* stg = lds + G::RING + wave * G::STAGING;
-      // Opaque copies of the values the addresses below derive from: without
-      // them the compiler computes those (entry- or lane-invariant) addresses
-      // before the steps and keeps them live across the step loop.
-      int ln = lane, q0 = qrow0, nv = nvalid, hg = g * a.group;
-      asm volatile("" : "+v"(ln), "+s"(q0), "+s"(nv), "+s"(hg));
-      const int l32e = ln & 31, halfe = ln >> 5;
-#pragma unroll
-      for (int rd = 0; rd < D / HD; ++rd) {
-#pragma unroll
-        for (int tt = 0; tt < TPR; ++tt)
-#pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
-            const int t = rd * TPR + tt, c = tt * 4 + gq;   // d = 32 t + 8 gq + 4 half ..
-            const u32x2 w{pack_bf16x2(oacc[t][gq * 4 + 0] * inv, oacc[t][gq * 4 + 1] * inv),
-                          pack_bf16x2(oacc[t][gq * 4 + 2] * inv, oacc[t][gq * 4 + 3] * inv)};
-            *reinterpret_cast<u32x2*>(stg + l32e * (HD * 2) + ((c ^ (l32e % CPR)) << 4) + halfe * 8) = w;
-          }
-        asm volatile("" ::: "memory");
-        // all of the round's reads first, then the stores of the rows that exist
-        u32x4 v[32 / RPI];
-#pragma unroll
-        for (int q = 0; q < 32 / RPI; ++q) {
-          const int r = q * RPI + ln / CPR, c = ln % CPR;
-          v[q] = *reinterpret_cast<const u32x4*>(stg + r * (HD * 2) + ((c ^ (r % CPR)) << 4));
-        }
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int q = 0; q < 32 / RPI; ++q) {
-          const int r = q * RPI + ln / CPR, c = ln % CPR;
-          // the staged row's column of the tile, its head and position
-          const uint32_t mr = uint32_t(wave * 32 + r);
-          const int hr = int((mr * tdiv) >> 16);
-          const int pr = int(mr) - hr * a.per_tile;
-          if (hr < a.group && pr < nv)
-            *reinterpret_cast<u32x4*>(a.out + ((int64_t(q0) + pr) * a.hq + hg + hr) * D + rd * HD + c * 8) = v[q];
-        }
-      }
+      store_output<D>(a, oacc, inv, tdiv, lds + G::RING + wave * G::STAGING, lane, wave, qrow0, nvalid, g * a.group);
     }
   }
   // Every copy the cursor issued was consumed: the cursor runs out with the
@@ -1629,29 +1646,8 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
   };
   const bool group1 = wave >= 4;
 
-  // ---- per-lane LDS read offsets (ring position 0; a position adds its stride)
-  // K operand: key 32 h + pi(l32) (block 2 h + l32 / 16, row pi(l32) % 16),
-  // chunk 2 s + half; in the chunk-major block layout that is the lane's base
-  // plus h 32 RB + s 512.
-  const int k_row = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-  int k_off = (l32 >> 4) * (kBs * RB) + half * 256 + (k_row & 15) * 16;
-  // V operand (transposing reads, two per operand): in each 16-lane group a
-  // lane names 4 values of d of one key, and lane 4 q + s receives value s of
-  // the 4 keys named by lanes q, q + 4, q + 8, q + 12. Lane j of group gq names
-  // key 8 half + 4 rd + j / 4 of the block (rd: first or second read) and
-  // d = 32 t + 16 (gq % 2) + 4 (j % 4), so lane l32 receives row d = 32 t + l32,
-  // keys 8 half + 4 rd .. + 3: with both reads the operand of keys
-  // 8 half .. + 7. In the swizzled chunk-major layout that is the lane's base
-  // (chunk c % 4 = 2 (gq % 2) + (j % 4) / 2) plus t 1024 + kk BLK.
-  const int vj = lane & 15, vpart = 2 * ((lane >> 4) & 1) + ((vj & 3) >> 1);
-  int v_off0 = KREG + vpart * 256 + (((8 * half + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
-  int v_off1 = KREG + vpart * 256 + (((8 * half + 4 + (vj >> 2)) ^ (4 * vpart)) << 4) + 8 * (vj & 1);
-  // Hide the bases' known bits from the compiler: otherwise it rewrites
-  // base + constant as base | constant, which it cannot fold into the LDS
-  // instructions' offset field, and keeps one register per read instead.
-  asm volatile("" : "+v"(k_off));
-  asm volatile("" : "+v"(v_off0));
-  asm volatile("" : "+v"(v_off1));
+  int k_off, v_off0, v_off1;
+  operand_offsets<D>(lane, l32, half, k_off, v_off0, v_off1);
   auto rd16 = [&](int addr) __attribute__((always_inline)) -> bf16x8 {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(lds + addr));
   };
@@ -1731,10 +1727,7 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : "+v"(d1) :: "memory");
   barrier();
 
-  // Output rows of the staged read-back : the lanes reading
-  // staged row rr hold column m' = 32 wave + rr of the tile, i.e. head m' / T
-  // and position m' % T (T = a.per_tile; the quotient by a multiply, exact for
-  // m' < 256).
+  // Divides a column of the tile (below 256) by a.per_tile (store_output).
   const uint32_t tdiv = (65536u + uint32_t(a.per_tile) - 1) / uint32_t(a.per_tile);
 
   f32x16 sc[2];      // scores of the step whose softmax comes next
@@ -1880,34 +1873,8 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
       }
       issue(p + (group1 ? 3 : 2));
 
-      // Causal mask of the step starting at key k0: element e of accumulator h
-      // holds key k0 + 32 h + (e / 8) 16 + half 8 + e % 8; the lane term moves to
-      // the limit so that the per-element terms stay immediates.
-      // (each element is pinned after its select: otherwise the compiler keeps
-      // all 32 compare results live as lane masks in scalar registers)
-      if (__builtin_expect(j >= n_full, 0)) {
-        const int lim = qpos - (kbeg + j) * kKv - half * 8;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int e2 = 0; e2 < 16; ++e2) {
-            if (h * 32 + (e2 >> 3) * 16 + (e2 & 7) > lim) sc[h][e2] = -INFINITY;
-            asm volatile("" : "+v"(sc[h][e2]));
-          }
-      }
-      // Maximum of the row over the step's 64 keys (this lane's 32 and lane ^ 32's).
-      float mx;
-      {
-        float x = fmaxf(fmaxf(sc[0][0], sc[0][1]), sc[0][2]);
-        float y = fmaxf(fmaxf(sc[1][0], sc[1][1]), sc[1][2]);
-#pragma unroll
-        for (int e2 = 3; e2 < 15; e2 += 2) {
-          x = fmaxf(fmaxf(x, sc[0][e2]), sc[0][e2 + 1]);
-          y = fmaxf(fmaxf(y, sc[1][e2]), sc[1][e2 + 1]);
-        }
-        x = fmaxf(fmaxf(x, sc[0][15]), sc[1][15]);
-        mx = max_pair32(fmaxf(x, y));
-      }
+      if (__builtin_expect(j >= n_full, 0)) causal_mask(sc, qpos - (kbeg + j) * kKv - half * 8);
+      const float mx = row_max(sc);
       if (__builtin_expect(j == 0, 0)) {
         // The first step's exact row maximum is the base. (Key 0 is visible to
         // every row, so it is finite unless every score of the step is -inf.)
@@ -1983,63 +1950,8 @@ void suffix_prefill_stream_kernel(const AttnArgs a) {
       d2 = *reinterpret_cast<const int32_t*>(lds + (own_words - lds0) + lane * 4);
       asm volatile("" : "+v"(d2) :: "memory");
       const float l_tot = sum_pair32(l_run);
-      {
-        // The output goes through this wave's staging area: a lane holds 4
-        // consecutive d of its row per (t, gq), so direct stores would write 32
-        // rows in 8-byte pieces per instruction. Each round stages a range of d
-        // (HD values) of all 32 rows and reads it back as rows of 16-byte
-        // chunks, so that each store covers whole 128-byte lines of HD values
-        // (16-byte chunk c of staged row r at position c ^ (r % CPR):
-        // conflict-free writes and reads). Lanes read what other lanes wrote:
-        // the hardware keeps a wave's LDS accesses in order, and empty asm
-        // statements with a memory clobber keep the compiler from reusing, for
-        // a lane, values it loaded before another lane's writes (as it may, for
-        // memory it sees no other thread write).
-        constexpr int HD = G::STAGING / (32 * 2);   // d values per round (64)
-        constexpr int CPR = HD / 8;                // 16-byte chunks per staged row
-        constexpr int TPR = HD / 32;               // output tiles per round
-        constexpr int RPI = 64 / CPR;              // staged rows per read instruction
-        static_assert(D % HD == 0 && CPR == 8, "staging rounds");
-        const float inv = row_ok ? __builtin_amdgcn_rcpf(l_tot) : 0.f;
-        uint8_t* stg = lds + G::RING + wave * G::STAGING;
-        // Opaque copies of the values the addresses below derive from: without
-        // them the compiler computes those (entry- or lane-invariant) addresses
-        // before the steps and keeps them live across the step loop.
-        int ln = lane, q0 = qrow0, nv = nvalid, hg = g * a.group;
-        asm volatile("" : "+v"(ln), "+s"(q0), "+s"(nv), "+s"(hg));
-        const int l32e = ln & 31, halfe = ln >> 5;
-#pragma unroll
-        for (int rd = 0; rd < D / HD; ++rd) {
-#pragma unroll
-          for (int tt = 0; tt < TPR; ++tt)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-              const int t = rd * TPR + tt, c = tt * 4 + gq;   // d = 32 t + 8 gq + 4 half ..
-              const u32x2 w2{pack_bf16x2(oacc[t][gq * 4 + 0] * inv, oacc[t][gq * 4 + 1] * inv),
-                             pack_bf16x2(oacc[t][gq * 4 + 2] * inv, oacc[t][gq * 4 + 3] * inv)};
-              *reinterpret_cast<u32x2*>(stg + l32e * (HD * 2) + ((c ^ (l32e % CPR)) << 4) + halfe * 8) = w2;
-            }
-          asm volatile("" ::: "memory");
-          // all of the round's reads first, then the stores of the rows that exist
-          u32x4 v[32 / RPI];
-#pragma unroll
-          for (int q = 0; q < 32 / RPI; ++q) {
-            const int r = q * RPI + ln / CPR, c = ln % CPR;
-            v[q] = *reinterpret_cast<const u32x4*>(stg + r * (HD * 2) + ((c ^ (r % CPR)) << 4));
-          }
-          asm volatile("" ::: "memory");
-#pragma unroll
-          for (int q = 0; q < 32 / RPI; ++q) {
-            const int r = q * RPI + ln / CPR, c = ln % CPR;
-            // the staged row's column of the tile, its head and position
-            const uint32_t mr = uint32_t(wave * 32 + r);
-            const int hr = int((mr * tdiv) >> 16);
-            const int pr = int(mr) - hr * a.per_tile;
-            if (hr < a.group && pr < nv)
-              *reinterpret_cast<u32x4*>(a.out + ((int64_t(q0) + pr) * a.hq + hg + hr) * D + rd * HD + c * 8) = v[q];
-          }
-        }
-      }
+      const float inv = row_ok ? __builtin_amdgcn_rcpf(l_tot) : 0.f;
+      store_output<D>(a, oacc, inv, tdiv, lds + G::RING + wave * G::STAGING, lane, wave, qrow0, nvalid, g * a.group);
 #pragma unroll
       for (int t = 0; t < DT; ++t) oacc[t] = f32x16{};
       l_run = 0.f;
